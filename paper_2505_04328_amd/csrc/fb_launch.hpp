@@ -31,6 +31,7 @@ struct FbHost {
     double ks[64];        // gamma^n and sqrt(V_n) for n = 0..31
     uint64_t thr[32];     // Poisson(rate dt) thresholds
     PoissonTable poisson;
+    void* small;          // the workspace's scratch of the small-count kernels (FbSmall)
 };
 
 // Per-step table in the path precision: mu rows (N x nx x nvp, zero-padded),
@@ -45,6 +46,28 @@ FbTable fb_table_layout(const FbHost& p);
 // variances, then the line a_x, a_v, b_x, b_v).
 size_t fb_mom_count(const FbHost& p, const HostRun& r);
 size_t fb_svar_count(const FbHost& p);
+
+// Small particle counts (fb_small.hip).  Whether a forward / an adjoint sweep
+// takes those kernels, their workspace scratch (byte offsets; total 0 when
+// they are not taken) and the forward's split over workgroups.
+constexpr int kFbSmallCoef = 6;      // coefficients of an adjoint step
+constexpr int kFbRowSlots = 16;      // particles per workgroup, independent particles
+constexpr int kFbRingRowSlots = 32;  // particles (with halos) per workgroup, rings
+inline int fb_row_slots(const FbHost& p) { return p.np == 1 ? kFbRowSlots : kFbRingRowSlots; }
+bool fb_small_forward_ok(const FbHost& p, const HostRun& r);
+bool fb_small_adjoint_ok(const FbHost& p, const HostRun& r);
+struct FbSmall {
+    size_t state, acc, coef, wgt, total;
+};
+FbSmall fb_small_layout(const FbHost& p, const HostRun& r);
+struct FbRowPlan {
+    int steps;        // steps per launch
+    int halo, own;    // ring segments: halo and own particles (own = 0: whole rings)
+    int nseg, rings;  // segments per ring, or whole rings per workgroup
+    int64_t blocks;
+};
+// The split of a sweep over workgroups of `slots` particles.
+FbRowPlan fb_row_plan(const FbHost& p, const HostRun& r, int slots);
 
 hipError_t fb_launch_table(const FbHost& p, const HostRun& r, const double* mu, void* tab,
                            WsHeader* hdr, int clear_flag, hipStream_t st, Gate gate = kNoGate);

@@ -1,0 +1,715 @@
+// Particle-model kernels for particle counts that leave most of the chip idle
+// (fb_small() in jd_shapes.cpp).  One particle per lane puts 2000 particles on
+// 32 of the 1024 SIMDs, and each step waits on one lane's chain: the control's
+// rows by scalar loads, the Philox rounds, the bumps one after another (2.5 us
+// per FP32 step against 0.15 us of issue).  Here the parallelism that a step
+// and a sweep do have is used instead:
+//
+//  k_fb_forward_rows  one particle per row of 16 lanes: lane j takes shape
+//                     function j of each axis and control row j, sums travel by
+//                     row broadcasts (DPP), the draws of 16 steps are computed
+//                     at once, one per lane; a ring is split over workgroups
+//                     with a halo
+//  k_fb_coef          everything of an adjoint step that does not depend on the
+//                     adjoint state, for all particle-steps at once
+//  k_fb_recur,        the adjoint recursion on those coefficients (a few
+//  k_fb_recur_ring    multiply-adds per step); writes the gradient weights
+//  k_fb_contract      the gradient's sum over particles of all steps at once,
+//                     with the matrix-core chains of k_fb_adjoint
+//
+// Every state, adjoint and weight is computed by the same operations in the
+// same order as in k_fb_forward and k_fb_adjoint, and the FP32 matrix-core
+// chains take the same particles in the same order, so only the order of FP64
+// sums differs.
+//
+// Measured (MI355X): 2000 particles x 50 steps of the 10 x 10 grid, FP32:
+// forward 127 -> 30 us, adjoint 109 -> 18 us (5.5 + 8.2 + 4.4); one FP64 ring of
+// 2000 x 50: 1055 -> 75 us (four launches) and 1015 -> 39 us (10 + 20 + 8.4).
+#include "fb_device.hpp"
+
+namespace jd {
+
+// ---------------------------------------------------------------------------
+// Row broadcasts: lane I of the caller's row of 16 lanes (DPP row_newbcast).
+template <int I>
+__device__ __forceinline__ float row_bcast(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
+        0, __builtin_bit_cast(int, v), 0x150 + I, 0xf, 0xf, true));
+}
+template <int I>
+__device__ __forceinline__ double row_bcast(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x150 + I, 0xf,
+                                                              0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32),
+                                                              0x150 + I, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
+// t <- fma(m[l], pv of lane l, t) for l = I .. W-1, in that order.
+template <typename Real, int W, int I = 0>
+__device__ __forceinline__ Real row_dot(const Real (&m)[W], Real pv, Real t) {
+    if constexpr (I < W)
+        return row_dot<Real, W, I + 1>(m, pv, fma(m[I], row_bcast<I>(pv), t));
+    else
+        return t;
+}
+// u <- fma(b of lane i, t of lane i, u) for i = I .. W-1, in that order.
+template <typename Real, int W, int I = 0>
+__device__ __forceinline__ Real row_sum(Real b, Real t, Real u) {
+    if constexpr (I < W)
+        return row_sum<Real, W, I + 1>(b, t, fma(row_bcast<I>(b), row_bcast<I>(t), u));
+    else
+        return u;
+}
+
+// The feedback control of the row's particle at (x, v), as fb_control: lane j
+// holds row j of the step's coefficients in m (zeros past the grid; a zero
+// term leaves a sum as it is).
+template <typename Real, int W>
+__device__ __forceinline__ Real row_control(const FbArgs<Real>& a, const Real (&m)[W], int j,
+                                            Real x, Real v) {
+    const Real bx = bump_q(fma(-(Real)j, a.eps * a.dxc, a.eps * (x - a.xc0)));
+    const Real pv = bump_q(fma(-(Real)j, a.eps * a.dvc, a.eps * (v - a.vc0)));
+    const Real t = row_dot<Real, W>(m, pv, (Real)0);
+    return row_sum<Real, W>(bx, t, (Real)0);
+}
+
+// Draws of one step: the Box-Muller cosine and sine branches, the jump normal
+// and the count (kept as a Real: one 16- or 32-byte LDS read brings all four).
+template <typename Real>
+struct alignas(4 * sizeof(Real)) FbRowDraw {
+    Real zc, zs, zj, n;
+};
+
+// Row of a step's coefficients in LDS, padded to 16-byte reads.
+constexpr int fb_row_stride(int W) { return (W + 3) / 4 * 4; }
+
+// The ring kernel's work split (see FbRowPlan) and the state carried between
+// its launches.
+template <typename Real>
+struct FbRows {
+    int k0, k1;       // steps of this launch
+    int nvp;          // row width of the control table
+    int halo, own;    // slots of a segment: halo, own, halo (own = 0: whole rings)
+    int nseg, rings;  // segments per ring, or whole rings per workgroup
+    Real* in;         // x, v, cx, cv of every particle at k0 (k0 > 0)
+    Real* out;        // the same at k1 (k1 < N)
+    double* acc;      // running cost of every particle
+};
+
+// Slot q of a ring workgroup of SL slots: own = 0: `rings` whole rings per
+// workgroup; else one of nseg segments of a ring, `own` particles with `halo`
+// more on either side.  act: an own particle; halo slots hold particles too
+// (p, slot: their trajectory slot) but write nothing.
+struct FbRingSlot {
+    int64_t p, slot;
+    bool act;
+    int lft, rgt;
+};
+template <int SL, typename Real>
+__device__ __forceinline__ FbRingSlot fb_ring_slot(const FbArgs<Real>& a, int own, int halo,
+                                                   int nseg, int rings, int q) {
+    FbRingSlot s;
+    int64_t r;
+    int pos;
+    if (own == 0) {
+        const int si = q / a.np;
+        pos = q - si * a.np;
+        r = (int64_t)blockIdx.x * rings + si;
+        s.act = si < rings && r < a.nsys;
+        s.lft = s.act ? si * a.np + (pos == 0 ? a.np - 1 : pos - 1) : q;
+        s.rgt = s.act ? si * a.np + (pos + 1 == a.np ? 0 : pos + 1) : q;
+        if (!s.act)
+            r = pos = 0;
+    } else {
+        r = blockIdx.x / nseg;
+        const int e = (int)(blockIdx.x - r * nseg) * own + q - halo;
+        s.act = q >= halo && q < halo + own && e < a.np;
+        pos = e % a.np;
+        pos = pos < 0 ? pos + a.np : pos;
+        s.lft = q > 0 ? q - 1 : 0;
+        s.rgt = q + 1 < SL ? q + 1 : q;
+    }
+    s.p = r * a.np + pos;
+    const int64_t wg = r / a.sb;
+    const int slots = a.np <= kThreads ? kThreads : kFbRingSlots;
+    s.slot = wg * slots + (r - wg * a.sb) * a.np + pos;
+    return s;
+}
+
+// Forward sweep, one particle per row of 16 lanes (TPB / 16 slots per
+// workgroup).  Rings: a step needs the neighbours' x_k, exchanged through LDS
+// with one barrier per step; a ring longer than the workgroup's slots is cut
+// into segments of `own` particles with `halo` more on either side.  v_{k+1}
+// takes the neighbours' x_k and x_{k+1} the own v_k, so a wrong value moves
+// one slot inward in two steps: after T <= 2 halo steps the own slots are
+// still exact.  A launch runs those T steps and hands the own particles' state
+// to the next launch.
+template <typename Real, int W, bool STORE, bool RING, int TPB>
+__global__ void __launch_bounds__(TPB)
+k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
+                  const Real* __restrict__ ks, void* traj, double* __restrict__ cpart,
+                  FbRows<Real> f) {
+    if (gate_closed(a.gate))
+        return;
+    constexpr int SL = TPB / 16;
+    constexpr int WS = fb_row_stride(W);
+    constexpr int NP = (16 * W * W + TPB - 1) / TPB;
+    __shared__ PoissonTable thr;
+    fb_stage_thresholds(a, &thr);
+    __shared__ Real ks_lds[64];
+    ks = fb_stage_ks(ks, ks_lds);
+    __shared__ alignas(16) Real mus[16][W][WS];
+    __shared__ FbRowDraw<Real> dr[SL][17];
+    __shared__ Real xs[RING ? 2 : 1][RING ? SL : 1];
+    __shared__ double sh[TPB];
+    const int row = threadIdx.x >> 4, j = threadIdx.x & 15;
+    // the row's particle
+    int64_t p, slot;
+    bool act;
+    int lft = row, rgt = row;
+    if constexpr (!RING) {
+        p = slot = (int64_t)blockIdx.x * SL + row;
+        act = p < a.M;
+    } else {
+        const FbRingSlot q = fb_ring_slot<SL>(a, f.own, f.halo, f.nseg, f.rings, row);
+        p = q.p;
+        slot = q.slot;
+        act = q.act;
+        lft = q.lft;
+        rgt = q.rgt;
+    }
+    Real x, v, cx = 0, cv = 0;
+    double acc = 0.0;
+    Real* trow = nullptr;
+    uint8_t* tcnt = nullptr;
+    const bool keep = RING ? act : slot < (int64_t)a.nblk * kThreads;
+    if (STORE) {
+        const int64_t b = keep ? slot / kThreads : 0;
+        const int l = (int)(slot % kThreads);
+        trow = (Real*)traj + (size_t)b * (a.N + 1) * 2 * kThreads + l;
+        tcnt = (uint8_t*)((Real*)traj + (size_t)a.nblk * (a.N + 1) * 2 * kThreads) +
+               (size_t)b * a.N * kThreads + l;
+    }
+    auto put = [&](int k) {
+        if (STORE && keep && j < 2)
+            trow[((size_t)k * 2 + j) * kThreads] = j == 0 ? x : v;
+        if (act && j == 0)
+            fb_dump(a, a.dX, k, p, x, v);
+    };
+    if (f.k0 == 0) {
+        fb_initial(a, (uint32_t)p, x, v);
+        put(0);
+    } else {
+        const Real* s = f.in + 4 * p;
+        x = s[0];
+        v = s[1];
+        cx = s[2];
+        cv = s[3];
+        if (act)
+            acc = f.acc[p];
+    }
+    // the next batch's control rows, loaded a batch ahead
+    Real pre[NP];
+    auto fetch = [&](int kb) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int e = q * TPB + (int)threadIdx.x;
+            const int s = e / (W * W), i = e / W % W, l = e % W;
+            const bool in = e < 16 * W * W && kb + s < f.k1 && i < a.nx && l < f.nvp;
+            pre[q] = in ? mu[((size_t)(kb + s) * a.nx + i) * f.nvp + l] : (Real)0;
+        }
+    };
+    fetch(f.k0);
+    for (int kb = f.k0; kb < f.k1; kb += 16) {
+        lds_barrier();  // the previous batch's readers are done
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int e = q * TPB + (int)threadIdx.x;
+            if (e < 16 * W * W)
+                mus[e / (W * W)][e / W % W][e % W] = pre[q];
+        }
+        if (kb + 16 < f.k1)
+            fetch(kb + 16);
+        {
+            // lane j: the draws of step kb + j
+            uint32_t w[4];
+            philox4x32_10<false>((uint32_t)p, (uint32_t)(kb + j), a.iter, 0u, a.key0, a.key1, w);
+            const Real R = bm_radius(w[0], (Real)0);
+            const Real ub = unit_uniform<Real>(w[1]);
+            FbRowDraw<Real> d;
+            d.zc = bm_cos(R, ub);
+            d.zs = bm_sin(R, ub);
+            d.zj = 0;
+            const int n = poisson_count(poisson_word(w), a.thr0, a.thr);
+            if (n != 0)
+                d.zj = bm_cos(bm_radius(w[2], (Real)0), unit_uniform<Real>(w[3]));
+            d.n = (Real)n;
+            dr[row][j] = d;
+        }
+        lds_barrier();
+        const int ns = f.k1 - kb < 16 ? f.k1 - kb : 16;
+        for (int s = 0; s < ns; ++s) {
+            const int k = kb + s;
+            const FbRowDraw<Real> d = dr[row][s];
+            if (RING && j == 0)
+                xs[k & 1][row] = x;
+            Real m[W];
+#pragma unroll
+            for (int l = 0; l < W; ++l)
+                m[l] = mus[s][j < W ? j : 0][l];
+            Real cpl = 0;
+            const Real u = row_control<Real, W>(a, m, j, x, v);
+            if (RING) {
+                lds_barrier();
+                const Real* xb = xs[k & 1];
+                cpl = a.omega * ((Real)2 * x - xb[lft] - xb[rgt]);
+            }
+            Real xn, vs, ex = 0, ev = 0;
+            if constexpr (sizeof(Real) == 4) {
+                xn = two_sum(x, fma(a.dt, v, fma(a.sqb1, d.zc, cx)), ex);
+                vs = two_sum(v, fma(a.dt, fma(-a.eta, x, u) - cpl, fma(a.sqb2, d.zs, cv)), ev);
+            } else {
+                xn = fma(a.sqb1, d.zc, fma(a.dt, v, x));
+                vs = fma(a.sqb2, d.zs, fma(a.dt, fma(-a.eta, x, u) - cpl, v));
+            }
+            if (d.n != (Real)0) {
+                Real gn, sv;
+                ks_factors(ks, (int)d.n, gn, sv);
+                vs = fma(sv, d.zj, gn * vs);
+                ev = gn * ev;
+            }
+            x = xn;
+            v = vs;
+            cx = ex;
+            cv = ev;
+            acc += (double)(a.hadt * u * u);
+            acc += (double)(a.dt * track(a, x, v, zd + 2 * (k + 1)));
+            put(k + 1);
+            if (STORE && keep && j == 2)
+                tcnt[(size_t)k * kThreads] = (uint8_t)(int)d.n;
+        }
+    }
+    if (f.k1 < a.N) {
+        if (act && j < 4)
+            f.out[4 * p + j] = j == 0 ? x : j == 1 ? v : j == 2 ? cx : cv;
+        if (act && j == 0)
+            f.acc[p] = acc;
+        return;
+    }
+    const double C = act && j == 0 ? acc : 0.0;
+    if (a.dcost != nullptr && act && j == 0) {
+        const int64_t e = p - a.dm0;
+        if (e >= 0 && e < a.dcount)
+            a.dcost[e] = C;
+    }
+    const double s = block_sum<TPB>(C, sh);
+    if (threadIdx.x == 0)
+        cpart[blockIdx.x] = s;
+}
+
+// ---------------------------------------------------------------------------
+// The particle in slot q of the trajectory (np = 1: slot = particle).
+template <typename Real>
+__device__ __forceinline__ FbSlot fb_slot_of(const FbArgs<Real>& a, int64_t q) {
+    FbSlot s;
+    s.lft = s.rgt = 0;
+    if (a.np == 1) {
+        s.act = q < a.M;
+        s.p = (uint32_t)q;
+        return s;
+    }
+    const int slots = a.np <= kThreads ? kThreads : kFbRingSlots;
+    const int64_t wg = q / slots;
+    const int o = (int)(q - wg * slots);
+    const int si = o / a.np, j = o - si * a.np;
+    const int64_t r = wg * a.sb + si;
+    s.act = si < a.sb && r < a.nsys;
+    s.p = s.act ? (uint32_t)(r * a.np + j) : (uint32_t)a.M;
+    return s;
+}
+
+// Coefficients of the adjoint step of one particle and step (k_fb_adjoint's
+// expressions without lam): values c = 0..5 of step k of block b's lane l at
+// coef[((b N + k) 6 + c) 256 + l].
+//   0 u   1 alpha u u_x + dJt/dx   2 gamma^n dt (u_x - eta [- 2 omega])
+//   3 alpha u u_v + dJt/dv   4 1 + dt u_v   5 gamma^n
+constexpr int kFbCoef = kFbSmallCoef;
+
+template <typename Real, int NVP>
+__global__ void __launch_bounds__(kThreads)
+k_fb_coef(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
+          const Real* __restrict__ ks, const void* traj, Real* __restrict__ coef) {
+    if (gate_closed(a.gate))
+        return;
+    const int b = blockIdx.x / a.N, k = blockIdx.x - b * a.N;
+    const bool act = fb_slot_of(a, (int64_t)b * kThreads + threadIdx.x).act;
+    const Real* row = fb_row<Real>(const_cast<void*>(traj), a.N, b) + (size_t)k * 2 * kThreads;
+    const uint8_t* cnt = (const uint8_t*)((const Real*)traj + (size_t)a.nblk * (a.N + 1) * 2 * kThreads) +
+                         ((size_t)b * a.N + k) * kThreads + threadIdx.x;
+    const Real x = act ? row[0] : (Real)0, v = act ? row[kThreads] : (Real)0;
+    const int n = act ? *cnt : 0;
+    Real gn = 1;
+    if (n != 0) {
+        Real svn;
+        ks_factors(ks, n, gn, svn);
+    }
+    const Real* mk = mu + (size_t)k * a.nx * NVP;
+    Real pv[NVP], dpv[NVP];
+#pragma unroll
+    for (int l = 0; l < NVP; ++l)
+        pv[l] = bump_dq(fma(-(Real)l, a.eps * a.dvc, a.eps * (v - a.vc0)), dpv[l]);
+    Real u = 0, ux = 0, uv = 0;
+#pragma unroll 2
+    for (int i = 0; i < a.nx; ++i) {
+        Real dbx;
+        const Real bx = bump_dq(fma(-(Real)i, a.eps * a.dxc, a.eps * (x - a.xc0)), dbx);
+        const Real* rw = mk + i * NVP;
+        Real t = 0, sv = 0;
+#pragma unroll
+        for (int l = 0; l < NVP; ++l) {
+            t = fma(rw[l], pv[l], t);
+            sv = fma(rw[l], dpv[l], sv);
+        }
+        u = fma(bx, t, u);
+        ux = fma(dbx, t, ux);
+        uv = fma(bx, sv, uv);
+    }
+    ux *= (Real)-2 * a.eps;  // d carries b'(r) / (-2 eps)
+    uv *= (Real)-2 * a.eps;
+    Real gx, gv;
+    track_grad(a, x, v, zd + 2 * k, gx, gv);
+    const Real au = a.alpha * u;
+    const Real sx = a.np > 1 ? ux - a.eta - (Real)2 * a.omega : ux - a.eta;
+    Real* c = coef + (size_t)blockIdx.x * kFbCoef * kThreads + threadIdx.x;
+    c[0] = u;
+    c[kThreads] = fma(au, ux, gx);
+    c[2 * kThreads] = gn * a.dt * sx;
+    c[3 * kThreads] = fma(au, uv, gv);
+    c[4 * kThreads] = fma(a.dt, uv, (Real)1);
+    c[5 * kThreads] = gn;
+}
+
+// lam_N of the particle in lane l of block b.
+template <typename Real>
+__device__ __forceinline__ void fb_lam_end(const FbArgs<Real>& a, const Real* __restrict__ zd,
+                                           const void* traj, int64_t b, int l, bool act, Real& lx,
+                                           Real& lv) {
+    const Real* row = (const Real*)traj + ((size_t)b * (a.N + 1) + a.N) * 2 * kThreads + l;
+    const Real x = act ? row[0] : (Real)0, v = act ? row[kThreads] : (Real)0;
+    Real gx, gv;
+    track_grad(a, x, v, zd + 2 * a.N, gx, gv);
+    lx = a.dt * gx;
+    lv = a.dt * gv;
+}
+
+// One step of the recursion on its coefficients: returns the gradient weight
+// alpha u + gamma^n lam^v and moves lam on; w: gamma^n lam^v_{k+1}.
+template <typename Real>
+__device__ __forceinline__ Real fb_recur_step(const FbArgs<Real>& a, const Real (&c)[kFbCoef],
+                                              Real& lx, Real& lv, Real& w) {
+    w = c[5] * lv;
+    const Real wk = fma(a.alpha, c[0], w);
+    const Real nlx = fma(a.dt, c[1], fma(c[2], lv, lx));
+    const Real nlv = fma(a.dt, c[3], fma(c[5], c[4] * lv, a.dt * lx));
+    lx = nlx;
+    lv = nlv;
+    return wk;
+}
+
+// The recursion of independent particles, one per lane, in workgroups of one
+// wave (so that few particles still spread over the chip).  A batch of steps'
+// coefficients is loaded while the batch before is swept: the sweep of a step
+// is a few dependent multiply-adds, so the loads' latency bounds the kernel and
+// the batch is as long as the registers allow (2000 x 50 FP32: 8.7 us with 8
+// steps, 8.2 us with 16).  Weights: wgt[(b N + k) 256 + l].
+template <typename Real>
+__global__ void __launch_bounds__(64)
+k_fb_recur(FbArgs<Real> a, const Real* __restrict__ zd, const void* traj,
+           const Real* __restrict__ coef, Real* __restrict__ wgt) {
+    if (gate_closed(a.gate))
+        return;
+    constexpr int U = sizeof(Real) == 4 ? 16 : 8;
+    const int64_t q = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const int64_t b = q / kThreads;
+    const int l = (int)(q % kThreads);
+    const FbSlot s = fb_slot_of(a, q);
+    Real lx, lv;
+    fb_lam_end(a, zd, traj, b, l, s.act, lx, lv);
+    if (s.act)
+        fb_dump(a, a.dlam, a.N, s.p, lx, lv);
+    const Real* cb = coef + (size_t)b * a.N * kFbCoef * kThreads + l;
+    Real* wb = wgt + (size_t)b * a.N * kThreads + l;
+    Real ca[U][kFbCoef], cc[U][kFbCoef];
+    auto load = [&](int k, Real (&c)[U][kFbCoef]) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int kk = k - i > 0 ? k - i : 0;
+#pragma unroll
+            for (int e = 0; e < kFbCoef; ++e)
+                c[i][e] = cb[((size_t)kk * kFbCoef + e) * kThreads];
+        }
+    };
+    auto sweep = [&](int k, const Real (&c)[U][kFbCoef]) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            if (k - i >= 0) {
+                Real w;
+                const Real wk = fb_recur_step(a, c[i], lx, lv, w);
+                wb[(size_t)(k - i) * kThreads] = s.act ? wk : (Real)0;
+                if (s.act && k - i >= 1)
+                    fb_dump(a, a.dlam, k - i, s.p, lx, lv);
+            }
+        }
+    };
+    int k = a.N - 1;
+    load(k, ca);
+    for (;;) {
+        if (k - U >= 0)
+            load(k - U, cc);
+        sweep(k, ca);
+        k -= U;
+        if (k < 0)
+            break;
+        if (k - U >= 0)
+            load(k - U, ca);
+        sweep(k, cc);
+        k -= U;
+        if (k < 0)
+            break;
+    }
+}
+
+// The recursion of rings, one particle per lane: a step adds dt omega (w_l + w_r)
+// of the neighbours, exchanged through LDS (double-buffered by step parity).
+// Rings longer than the workgroup are cut into segments with halos, steps
+// k1 - 1 .. k0 per launch, as in k_fb_forward_rows (lam^x_k takes the
+// neighbours' lam^v_{k+1} and lam^v_k the own lam^x_{k+1}: a wrong value moves
+// one slot in two steps).
+template <typename Real>
+__global__ void __launch_bounds__(kThreads)
+k_fb_recur_ring(FbArgs<Real> a, const Real* __restrict__ zd, const void* traj,
+                const Real* __restrict__ coef, Real* __restrict__ wgt, FbRows<Real> f) {
+    if (gate_closed(a.gate))
+        return;
+    constexpr int U = 8;
+    __shared__ Real cw[2][kThreads];
+    const FbRingSlot s = fb_ring_slot<kThreads>(a, f.own, f.halo, f.nseg, f.rings,
+                                                (int)threadIdx.x);
+    const int64_t b = s.slot / kThreads;
+    const int l = (int)(s.slot % kThreads);
+    Real lx, lv;
+    if (f.k1 == a.N) {
+        fb_lam_end(a, zd, traj, b, l, true, lx, lv);
+        if (s.act)
+            fb_dump(a, a.dlam, a.N, s.p, lx, lv);
+    } else {
+        lx = f.in[2 * s.p];
+        lv = f.in[2 * s.p + 1];
+    }
+    const Real* cb = coef + (size_t)b * a.N * kFbCoef * kThreads + l;
+    Real* wb = wgt + (size_t)b * a.N * kThreads + l;
+    const Real dto = a.dt * a.omega;
+    Real ca[U][kFbCoef], cc[U][kFbCoef];
+    auto load = [&](int k, Real (&c)[U][kFbCoef]) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int kk = k - i > f.k0 ? k - i : f.k0;
+#pragma unroll
+            for (int e = 0; e < kFbCoef; ++e)
+                c[i][e] = cb[((size_t)kk * kFbCoef + e) * kThreads];
+        }
+    };
+    auto sweep = [&](int k, const Real (&c)[U][kFbCoef]) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            if (k - i >= f.k0) {
+                Real w;
+                const Real wk = fb_recur_step(a, c[i], lx, lv, w);
+                Real* wx = cw[(k - i) & 1];
+                wx[threadIdx.x] = w;
+                if (s.act)
+                    wb[(size_t)(k - i) * kThreads] = wk;
+                lds_barrier();
+                lx = fma(dto, wx[s.lft] + wx[s.rgt], lx);
+                if (s.act && k - i >= 1)
+                    fb_dump(a, a.dlam, k - i, s.p, lx, lv);
+            }
+        }
+    };
+    int k = f.k1 - 1;
+    load(k, ca);
+    for (;;) {
+        if (k - U >= f.k0)
+            load(k - U, cc);
+        sweep(k, ca);
+        k -= U;
+        if (k < f.k0)
+            break;
+        if (k - U >= f.k0)
+            load(k - U, ca);
+        sweep(k, cc);
+        k -= U;
+        if (k < f.k0)
+            break;
+    }
+    if (f.k0 > 0 && s.act) {
+        f.out[2 * s.p] = lx;
+        f.out[2 * s.p + 1] = lv;
+    }
+}
+
+// The gradient's sum over particles of one step and one partial column: the
+// four waves of a workgroup each run k_fb_adjoint's matrix-core chain over 64 G
+// slots (G = 2: two groups of 64, kFbRingSlots / 2 apart, as the ring kernel's
+// lanes carry them), and the four tiles are summed in FP64.
+template <typename Real, int NVP, int G>
+__global__ void __launch_bounds__(kThreads)
+k_fb_contract(FbArgs<Real> a, const void* traj, const Real* __restrict__ wgt,
+              double* __restrict__ apart) {
+    if (gate_closed(a.gate))
+        return;
+    __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
+    auto wave = fb_wave(sh);
+    const int N = a.N, col = blockIdx.x / N, k = blockIdx.x - col * N;
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        // trajectory block and lane of the slot
+        int64_t b = col;
+        if (G == 2) {
+            const int half = kFbRingSlots / 2 / kThreads;
+            b = (int64_t)(col / half) * 2 * half + g * half + col % half;
+        }
+        const Real* row = fb_row<Real>(const_cast<void*>(traj), N, b) + (size_t)k * 2 * kThreads;
+        const bool act = fb_slot_of(a, b * kThreads + threadIdx.x).act;
+        const Real x = act ? row[0] : (Real)0, v = act ? row[kThreads] : (Real)0;
+        const Real w = act ? wgt[((size_t)b * N + k) * kThreads + threadIdx.x] : (Real)0;
+        Real pv[NVP];
+        shapes_v<Real, NVP>(a, v, pv);
+        for (int i = 0; i < a.nx; ++i)
+            wave.put_x(i, bump_q(fma(-(Real)i, a.eps * a.dxc, a.eps * (x - a.xc0))));
+        wave.template put_vw<Real, NVP>(pv, w);
+        wave.add();
+    }
+    FbHist<1> hist;
+    hist.cnt = 0;
+    hist.push(fb_tile(wave));
+    // the flush writes partial column blockIdx.x of one step: column
+    // (col N + k) as the block, step 0 of 1
+    fb_hist_flush<false>(sh, wave, hist, 0, 1, 1, a.nx, a.nv, apart);
+}
+
+// ===========================================================================
+// Launchers.
+
+template <typename Real>
+static FbRows<Real> fb_rows(const FbHost& p, const FbRowPlan& pl) {
+    FbRows<Real> f{};
+    f.nvp = p.nvp;
+    f.halo = pl.halo;
+    f.own = pl.own;
+    f.nseg = pl.nseg;
+    f.rings = pl.rings;
+    return f;
+}
+
+template <typename Real>
+hipError_t fb_small_forward(const FbHost& p, const HostRun& r, const void* tab, void* traj,
+                            double* cpart, const WsHeader* hdr, hipStream_t st, Gate gate) {
+    const FbTable t = fb_table_layout(p);
+    FbArgs<Real> a = fb_args<Real>(p, r);
+    a.thr = &hdr->poisson;
+    a.gate = gate;
+    const Real* tb = (const Real*)tab;
+    const FbSmall sm = fb_small_layout(p, r);
+    const FbRowPlan pl = fb_row_plan(p, r, fb_row_slots(p));
+    FbRows<Real> f = fb_rows<Real>(p, pl);
+    Real* state = (Real*)((char*)p.small + sm.state);
+    f.acc = (double*)((char*)p.small + sm.acc);
+    for (int k0 = 0, c = 0; k0 < p.N; k0 += pl.steps, ++c) {
+        f.k0 = k0;
+        f.k1 = p.N - k0 < pl.steps ? p.N : k0 + pl.steps;
+        // two state buffers in turn: a segment's neighbours read this launch's
+        // input while it writes its output
+        f.in = state + (size_t)(c & 1) * 4 * r.M;
+        f.out = state + (size_t)((c + 1) & 1) * 4 * r.M;
+#define FB_ROWS(W, S, RG, TPB)                                                                    \
+    hipLaunchKernelGGL((k_fb_forward_rows<Real, W, S, RG, TPB>), dim3((unsigned)pl.blocks),       \
+                       dim3(TPB), 0, st, a, tb + t.mu, tb + t.zd, tb + t.ks, traj, cpart, f)
+#define FB_ROWS_R(W, S)                                                                           \
+    do {                                                                                          \
+        if (p.np == 1) FB_ROWS(W, S, false, 16 * kFbRowSlots);                                    \
+        else FB_ROWS(W, S, true, 16 * kFbRingRowSlots);                                           \
+    } while (0)
+        if (p.nx <= 10 && p.nv <= 10) {
+            if (traj != nullptr) FB_ROWS_R(10, true);
+            else FB_ROWS_R(10, false);
+        } else {
+            if (traj != nullptr) FB_ROWS_R(16, true);
+            else FB_ROWS_R(16, false);
+        }
+#undef FB_ROWS_R
+#undef FB_ROWS
+    }
+    return hipGetLastError();
+}
+
+template <typename Real>
+hipError_t fb_small_adjoint(const FbHost& p, const HostRun& r, const void* tab, const void* traj,
+                            double* apart, hipStream_t st, Gate gate) {
+    const FbTable t = fb_table_layout(p);
+    FbArgs<Real> a = fb_args<Real>(p, r);
+    a.gate = gate;
+    const Real* tb = (const Real*)tab;
+    const FbSmall sm = fb_small_layout(p, r);
+    Real* coef = (Real*)((char*)p.small + sm.coef);
+    Real* wgt = (Real*)((char*)p.small + sm.wgt);
+    const unsigned nb = (unsigned)r.nblk;
+    const unsigned cells = nb * (unsigned)p.N;
+    const unsigned cols = (unsigned)fb_partial_blocks(p, r) * (unsigned)p.N;
+#define FB_COEF(NVP)                                                                              \
+    hipLaunchKernelGGL((k_fb_coef<Real, NVP>), dim3(cells), dim3(kThreads), 0, st, a, tb + t.mu,  \
+                       tb + t.zd, tb + t.ks, traj, coef)
+    FB_DISPATCH_NVP(p.nvp, FB_COEF);
+#undef FB_COEF
+    if (p.np == 1) {
+        hipLaunchKernelGGL(k_fb_recur<Real>, dim3(nb * (kThreads / 64)), dim3(64), 0, st, a,
+                           tb + t.zd, traj, coef, wgt);
+    } else {
+        const FbRowPlan pl = fb_row_plan(p, r, kThreads);
+        FbRows<Real> f = fb_rows<Real>(p, pl);
+        Real* state = (Real*)((char*)p.small + sm.state);
+        for (int k1 = p.N, c = 0; k1 > 0; k1 -= pl.steps, ++c) {
+            f.k1 = k1;
+            f.k0 = k1 > pl.steps ? k1 - pl.steps : 0;
+            f.in = state + (size_t)(c & 1) * 2 * r.M;
+            f.out = state + (size_t)((c + 1) & 1) * 2 * r.M;
+            hipLaunchKernelGGL(k_fb_recur_ring<Real>, dim3((unsigned)pl.blocks), dim3(kThreads), 0,
+                               st, a, tb + t.zd, traj, coef, wgt, f);
+        }
+    }
+#define FB_CON(NVP)                                                                               \
+    do {                                                                                          \
+        if (p.G == 1)                                                                             \
+            hipLaunchKernelGGL((k_fb_contract<Real, NVP, 1>), dim3(cols), dim3(kThreads), 0, st,  \
+                               a, traj, wgt, apart);                                              \
+        else                                                                                      \
+            hipLaunchKernelGGL((k_fb_contract<Real, NVP, 2>), dim3(cols), dim3(kThreads), 0, st,  \
+                               a, traj, wgt, apart);                                              \
+    } while (0)
+    FB_DISPATCH_NVP(p.nvp, FB_CON);
+#undef FB_CON
+    return hipGetLastError();
+}
+
+template hipError_t fb_small_forward<float>(const FbHost&, const HostRun&, const void*, void*,
+                                            double*, const WsHeader*, hipStream_t, Gate);
+template hipError_t fb_small_forward<double>(const FbHost&, const HostRun&, const void*, void*,
+                                             double*, const WsHeader*, hipStream_t, Gate);
+template hipError_t fb_small_adjoint<float>(const FbHost&, const HostRun&, const void*, const void*,
+                                            double*, hipStream_t, Gate);
+template hipError_t fb_small_adjoint<double>(const FbHost&, const HostRun&, const void*,
+                                             const void*, double*, hipStream_t, Gate);
+
+}  // namespace jd

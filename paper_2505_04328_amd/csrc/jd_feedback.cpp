@@ -155,7 +155,7 @@ int fb_prepare(const jd_fb_problem* prob, const jd_run* run, FbHost& p, HostRun&
 }
 
 struct FbLayout {
-    size_t hdr, ring, tab, cpart, apart, gbuf, ut, mom, svar, total;
+    size_t hdr, ring, tab, cpart, apart, gbuf, ut, mom, svar, small, total;
 };
 
 FbLayout fb_layout(const FbHost& p, const HostRun& r) {
@@ -168,7 +168,8 @@ FbLayout fb_layout(const FbHost& p, const HostRun& r) {
     L.tab = off;
     off += round_up(fb_table_layout(p).count * real_size(r.prec), kAlign);
     L.cpart = off;
-    off += round_up((size_t)r.nblk * sizeof(double), kAlign);
+    const int fwd = fb_forward_blocks(p, r);
+    off += round_up((size_t)(r.nblk > fwd ? r.nblk : fwd) * sizeof(double), kAlign);
     L.apart = off;
     off += round_up((size_t)r.nblk * p.N * p.L * sizeof(double), kAlign);
     L.gbuf = off;
@@ -183,6 +184,8 @@ FbLayout fb_layout(const FbHost& p, const HostRun& r) {
     L.svar = off;
     if (r.mode == JD_SURROGATE)
         off += round_up(fb_svar_count(p) * sizeof(double), kAlign);
+    L.small = off;
+    off += round_up(fb_small_layout(p, r).total, kAlign);
     L.total = off + kAlign;
     return L;
 }
@@ -207,7 +210,7 @@ struct FbWs {
     double* svar;  // surrogate: per-step variance and the variance line
 };
 
-int fb_bind(const FbHost& p, const HostRun& r, void* ws, size_t ws_bytes, FbWs& w) {
+int fb_bind(FbHost& p, const HostRun& r, void* ws, size_t ws_bytes, FbWs& w) {
     if (!ws)
         return JD_EINVAL;
     const FbLayout L = fb_layout(p, r);
@@ -223,6 +226,7 @@ int fb_bind(const FbHost& p, const HostRun& r, void* ws, size_t ws_bytes, FbWs& 
     w.ut = (double*)(base + L.ut);
     w.mom = (double*)(base + L.mom);
     w.svar = (double*)(base + L.svar);
+    p.small = base + L.small;
     return JD_OK;
 }
 

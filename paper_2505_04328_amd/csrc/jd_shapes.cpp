@@ -72,7 +72,90 @@ size_t fb_svar_count(const FbHost& p) { return (size_t)(p.N + 1) * 2 + 4; }
 
 int fb_ring_groups(int np) { return np <= kBlock ? 1 : 8; }
 
+// Where the small-count kernels (fb_small.hip) take over, 50 steps of the
+// 10 x 10 grid on an MI355X.
+//
+// Forward: a row kernel's time grows with the slots it computes (a segment's
+// halos included), the lane kernels' stays flat up to one wave per SIMD
+// (65536 particles) and, for rings of more than 256 particles, one workgroup per
+// CU.  Row / lane, FP32: 44 / 141 us at 2000 particles, 111 / 134 at 32768,
+// 189 / 136 at 65536; FP64 58 / 276, 228 / 257, 431 / 261.  Rings of 8..256, by
+// computed slots: FP32 130 / 147 at 32000, 234 / 147 at 71680; FP64 155 / 268 at
+// 8960, 296 / 270 at 32000.  Rings of 500 and 2000: FP32 298 / 334 at 96000, 329 /
+// 334 at 128000; FP64 827 / 1080 at 96000.
+static int64_t fb_small_forward_max(const FbHost& p, const HostRun& r) {
+    if (p.np > 1 && p.G > 1)
+        return 98304;
+    return p.np > 1 && r.prec == JD_FP64 ? 24576 : 32768;
+}
+// Adjoint, split / one kernel: FP32 33 / 162 us at 2000 particles, 72 / 163 at
+// 32768, 118 / 169 at 65536 (the whole gradient 260 / 267), 171 / 172 at 100000 (309 /
+// 287); FP64 139 / 230 at 32768, 201 / 233 at 48000, 265 / 236 at 64000.  Rings of
+// more than 256: FP32 363 / 454 at 200000, 447 / 458 at 256000; FP64 894 / 1080 at
+// 200000, 1107 / 1083 at 256000.
+static int64_t fb_small_adjoint_max(const FbHost& p, const HostRun& r) {
+    if (p.np > 1 && p.G > 1)
+        return 200000;
+    return r.prec == JD_FP64 ? 49152 : 65536;
+}
+// The coefficients of all particle-steps stay in the workspace.
+constexpr size_t kFbSmallMaxBytes = (size_t)1 << 30;
+
+bool fb_small_adjoint_ok(const FbHost& p, const HostRun& r) {
+    return p.grid == 0 && r.mode == JD_STORE && r.M <= fb_small_adjoint_max(p, r) &&
+           (size_t)r.ldm * (size_t)p.N * (kFbSmallCoef + 1) * real_size(r.prec) <= kFbSmallMaxBytes;
+}
+
+// The row forward leaves the empty slots of a ring workgroup unwritten, which
+// only the split adjoint masks.
+bool fb_small_forward_ok(const FbHost& p, const HostRun& r) {
+    if (p.grid != 0 || (p.np > 1 && !fb_small_adjoint_ok(p, r)))
+        return false;
+    const int slots = fb_row_slots(p);
+    return fb_row_plan(p, r, slots).blocks * slots <= fb_small_forward_max(p, r);
+}
+
+FbSmall fb_small_layout(const FbHost& p, const HostRun& r) {
+    FbSmall s{};
+    auto up = [](size_t x) { return (x + 255) / 256 * 256; };
+    size_t off = 0;
+    const bool adj = fb_small_adjoint_ok(p, r);
+    const bool rings = p.np > 1 && adj;  // segments' state between launches
+    s.state = off;
+    off += rings ? up((size_t)2 * 4 * r.M * real_size(r.prec)) : 0;
+    s.acc = off;
+    off += rings ? up((size_t)r.M * sizeof(double)) : 0;
+    const size_t cells = (size_t)r.ldm * p.N * real_size(r.prec);
+    s.coef = off;
+    off += adj ? up(cells * kFbSmallCoef) : 0;
+    s.wgt = off;
+    off += adj ? up(cells) : 0;
+    s.total = off;
+    return s;
+}
+
+FbRowPlan fb_row_plan(const FbHost& p, const HostRun& r, int slots) {
+    FbRowPlan q{};
+    q.steps = p.N;
+    if (p.np == 1) {
+        q.blocks = r.ldm / slots;
+    } else if (p.np <= slots) {
+        q.rings = slots / p.np;
+        q.blocks = (p.nsys + q.rings - 1) / q.rings;
+    } else {
+        // a quarter of the slots as halo on either side: half the work is own
+        q.halo = slots / 4;
+        q.steps = 2 * q.halo;
+        q.own = slots - 2 * q.halo;
+        q.nseg = (p.np + q.own - 1) / q.own;
+        q.blocks = p.nsys * q.nseg;
+    }
+    return q;
+}
+
 int fb_forward_blocks(const FbHost& p, const HostRun& r) {
+    if (fb_small_forward_ok(p, r))
+        return (int)fb_row_plan(p, r, fb_row_slots(p)).blocks;
     return p.np == 1 ? r.nblk : r.nblk / p.G;
 }
 
@@ -91,6 +174,8 @@ int fb_adjoint_groups(const FbHost& p, const HostRun& r) {
 }
 
 int fb_partial_blocks(const FbHost& p, const HostRun& r) {
+    if (p.np > 1 && fb_small_adjoint_ok(p, r))
+        return p.G == 1 ? r.nblk : r.nblk / 2;  // two 256-slot groups per column
     const int G = fb_adjoint_groups(p, r);
     return (r.nblk + G - 1) / G;
 }
