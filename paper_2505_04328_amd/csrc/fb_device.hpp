@@ -5,6 +5,8 @@
 // functions here, so that they agree bit for bit.
 #pragma once
 
+#include <type_traits>
+
 #include "fb_launch.hpp"
 #include "jd_device.hpp"
 
@@ -160,6 +162,123 @@ __device__ __forceinline__ void shapes_v(const FbArgs<Real>& a, Real v, Real* pv
 #pragma unroll
     for (int l = 0; l < NVP; ++l)
         pv[l] = bump_q(fma(-(Real)l, a.eps * a.dvc, a.eps * (v - a.vc0)));
+}
+
+// ---------------------------------------------------------------------------
+// Sums over a row of 16 lanes, lane by lane in a fixed order, by DPP row
+// broadcasts (row_newbcast:i reads lane i of the caller's row).  Written out
+// because the broadcast is an operand of the multiply-add itself: the compiler
+// spends a move per broadcast (row forward of 32768 particles x 50: 111 -> 101 us).  Every lane of the wave
+// must be active.  The leading s_nop is the distance a DPP operand needs from
+// the instruction that wrote it, and a use from a transcendental.
+#define JD_ROW_DPP(i) " row_newbcast:" #i " row_mask:0xf bank_mask:0xf\n\t"
+#define JD_ROW_DOT(F, i, o) "v_fmac_" F "_dpp %0, %1, %" #o JD_ROW_DPP(i)
+#define JD_ROW_DOT4(F) JD_ROW_DOT(F, 0, 2) JD_ROW_DOT(F, 1, 3) JD_ROW_DOT(F, 2, 4) JD_ROW_DOT(F, 3, 5)
+#define JD_ROW_DOT8(F) JD_ROW_DOT4(F) JD_ROW_DOT(F, 4, 6) JD_ROW_DOT(F, 5, 7) JD_ROW_DOT(F, 6, 8) JD_ROW_DOT(F, 7, 9)
+#define JD_ROW_DOT10(F) JD_ROW_DOT8(F) JD_ROW_DOT(F, 8, 10) JD_ROW_DOT(F, 9, 11)
+#define JD_ROW_DOT12(F) JD_ROW_DOT10(F) JD_ROW_DOT(F, 10, 12) JD_ROW_DOT(F, 11, 13)
+#define JD_ROW_DOT16(F) JD_ROW_DOT12(F) JD_ROW_DOT(F, 12, 14) JD_ROW_DOT(F, 13, 15) JD_ROW_DOT(F, 14, 16) JD_ROW_DOT(F, 15, 17)
+#define JD_ROW_M4 "v"(m[0]), "v"(m[1]), "v"(m[2]), "v"(m[3])
+#define JD_ROW_M8 JD_ROW_M4, "v"(m[4]), "v"(m[5]), "v"(m[6]), "v"(m[7])
+#define JD_ROW_M10 JD_ROW_M8, "v"(m[8]), "v"(m[9])
+#define JD_ROW_M12 JD_ROW_M10, "v"(m[10]), "v"(m[11])
+#define JD_ROW_M16 JD_ROW_M12, "v"(m[12]), "v"(m[13]), "v"(m[14]), "v"(m[15])
+#define JD_ROW_DOT_ASM(F, W) asm("s_nop 1\n\t" JD_ROW_DOT##W(F) : "+v"(t) : "v"(pv), JD_ROW_M##W)
+
+// t + sum_l m[l] (pv of lane l), l = 0 .. W-1 in order.
+template <typename Real, int W>
+__device__ __forceinline__ Real row_dot(const Real (&m)[W], Real pv, Real t) {
+    static_assert(W == 4 || W == 8 || W == 10 || W == 12 || W == 16, "a compiled row width");
+    if constexpr (sizeof(Real) == 4) {
+        if constexpr (W == 4) JD_ROW_DOT_ASM("f32", 4);
+        if constexpr (W == 8) JD_ROW_DOT_ASM("f32", 8);
+        if constexpr (W == 10) JD_ROW_DOT_ASM("f32", 10);
+        if constexpr (W == 12) JD_ROW_DOT_ASM("f32", 12);
+        if constexpr (W == 16) JD_ROW_DOT_ASM("f32", 16);
+    } else {
+        if constexpr (W == 4) JD_ROW_DOT_ASM("f64", 4);
+        if constexpr (W == 8) JD_ROW_DOT_ASM("f64", 8);
+        if constexpr (W == 10) JD_ROW_DOT_ASM("f64", 10);
+        if constexpr (W == 12) JD_ROW_DOT_ASM("f64", 12);
+        if constexpr (W == 16) JD_ROW_DOT_ASM("f64", 16);
+    }
+    return t;
+}
+
+// sum_i (b of lane i) (t of lane i), i = 0 .. W-1 in order; p, q: scratch.
+#define JD_ROW_SUM2(F, B, i, j)                                                                   \
+    "v_mov_" B "_dpp %1, %4" JD_ROW_DPP(i) "v_mov_" B "_dpp %2, %4" JD_ROW_DPP(j)                 \
+    "v_fmac_" F "_dpp %0, %3, %1" JD_ROW_DPP(i) "v_fmac_" F "_dpp %0, %3, %2" JD_ROW_DPP(j)
+#define JD_ROW_SUM10(F, B)                                                                        \
+    JD_ROW_SUM2(F, B, 0, 1) JD_ROW_SUM2(F, B, 2, 3) JD_ROW_SUM2(F, B, 4, 5)                       \
+    JD_ROW_SUM2(F, B, 6, 7) JD_ROW_SUM2(F, B, 8, 9)
+#define JD_ROW_SUM16(F, B)                                                                        \
+    JD_ROW_SUM10(F, B) JD_ROW_SUM2(F, B, 10, 11) JD_ROW_SUM2(F, B, 12, 13)                        \
+    JD_ROW_SUM2(F, B, 14, 15)
+#define JD_ROW_SUM_ASM(F, B, W)                                                                   \
+    asm("s_nop 1\n\t" JD_ROW_SUM##W(F, B) : "+v"(u), "=&v"(p), "=&v"(q) : "v"(b), "v"(t))
+template <typename Real, int W>
+__device__ __forceinline__ Real row_sum(Real b, Real t) {
+    static_assert(W == 10 || W == 16, "a compiled row count");
+    Real u = 0, p, q;
+    if constexpr (sizeof(Real) == 4) {
+        if constexpr (W == 10) JD_ROW_SUM_ASM("f32", "b32", 10);
+        else JD_ROW_SUM_ASM("f32", "b32", 16);
+    } else {
+        if constexpr (W == 10) JD_ROW_SUM_ASM("f64", "b64", 10);
+        else JD_ROW_SUM_ASM("f64", "b64", 16);
+    }
+    return u;
+}
+
+// The three sums of the control and its derivatives in one pass:
+// u = sum b t, ux = sum db t, uv = sum b s.
+#define JD_ROW_GRAD(F, B, i)                                                                      \
+    "v_mov_" B "_dpp %3, %7" JD_ROW_DPP(i) "v_mov_" B "_dpp %4, %8" JD_ROW_DPP(i)                 \
+    "v_fmac_" F "_dpp %0, %5, %3" JD_ROW_DPP(i) "v_fmac_" F "_dpp %1, %6, %3" JD_ROW_DPP(i)       \
+    "v_fmac_" F "_dpp %2, %5, %4" JD_ROW_DPP(i)
+#define JD_ROW_GRAD10(F, B)                                                                       \
+    JD_ROW_GRAD(F, B, 0) JD_ROW_GRAD(F, B, 1) JD_ROW_GRAD(F, B, 2) JD_ROW_GRAD(F, B, 3)           \
+    JD_ROW_GRAD(F, B, 4) JD_ROW_GRAD(F, B, 5) JD_ROW_GRAD(F, B, 6) JD_ROW_GRAD(F, B, 7)           \
+    JD_ROW_GRAD(F, B, 8) JD_ROW_GRAD(F, B, 9)
+#define JD_ROW_GRAD16(F, B)                                                                       \
+    JD_ROW_GRAD10(F, B) JD_ROW_GRAD(F, B, 10) JD_ROW_GRAD(F, B, 11) JD_ROW_GRAD(F, B, 12)         \
+    JD_ROW_GRAD(F, B, 13) JD_ROW_GRAD(F, B, 14) JD_ROW_GRAD(F, B, 15)
+#define JD_ROW_GRAD_ASM(F, B, W)                                                                  \
+    asm("s_nop 1\n\t" JD_ROW_GRAD##W(F, B)                                                        \
+        : "+v"(u), "+v"(ux), "+v"(uv), "=&v"(p), "=&v"(q)                                         \
+        : "v"(b), "v"(db), "v"(t), "v"(s))
+template <typename Real, int W>
+__device__ __forceinline__ void row_sum_grad(Real b, Real db, Real t, Real s, Real& u, Real& ux,
+                                             Real& uv) {
+    static_assert(W == 10 || W == 16, "a compiled row count");
+    Real p, q;
+    u = ux = uv = 0;
+    if constexpr (sizeof(Real) == 4) {
+        if constexpr (W == 10) JD_ROW_GRAD_ASM("f32", "b32", 10);
+        else JD_ROW_GRAD_ASM("f32", "b32", 16);
+    } else {
+        if constexpr (W == 10) JD_ROW_GRAD_ASM("f64", "b64", 10);
+        else JD_ROW_GRAD_ASM("f64", "b64", 16);
+    }
+}
+
+// The control of one particle per row of 16 lanes with its derivatives, as the
+// adjoint kernels evaluate them: lane j holds row j of the step's coefficients
+// in m (zeros past the grid; a zero term leaves a sum as it is).  Returns u, u_x
+// and u_v in every lane of the row, and the lane's shape values bx, pv.
+template <typename Real, int NVP, int W>
+__device__ __forceinline__ void row_control_grad(const FbArgs<Real>& a, const Real (&m)[NVP], int j,
+                                                 Real x, Real v, Real& bx, Real& pv, Real& u,
+                                                 Real& ux, Real& uv) {
+    Real dbx, dpv;
+    bx = bump_dq(fma(-(Real)j, a.eps * a.dxc, a.eps * (x - a.xc0)), dbx);
+    pv = bump_dq(fma(-(Real)j, a.eps * a.dvc, a.eps * (v - a.vc0)), dpv);
+    const Real t = row_dot<Real, NVP>(m, pv, (Real)0);
+    const Real sv = row_dot<Real, NVP>(m, dpv, (Real)0);
+    row_sum_grad<Real, W>(bx, dbx, t, sv, u, ux, uv);
+    ux *= (Real)-2 * a.eps;  // d carries b'(r) / (-2 eps)
+    uv *= (Real)-2 * a.eps;
 }
 
 // Receives the shape-function values a step computes, and the control u
@@ -449,6 +568,14 @@ struct FbMma<double> {
         return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ int row(int ln, int r) { return 4 * r + (ln >> 4); }
+    // a tile in LDS: entry (i, j), and the lane's four entries written
+    static constexpr int tile = 256;
+    static constexpr __host__ __device__ int at(int i, int j) { return i * 16 + j; }
+    static __device__ __forceinline__ void put(double* t, int ln, const acc_t& d) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            t[at(row(ln, r), ln & 15)] = d[r];
+    }
 };
 template <>
 struct FbMma<float> {
@@ -457,6 +584,12 @@ struct FbMma<float> {
         return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
     static __device__ __forceinline__ int row(int ln, int r) { return 4 * (ln >> 4) + r; }
+    // column by column, so that a lane's four rows are one 16-byte write
+    static constexpr int tile = 16 * 20;
+    static constexpr __host__ __device__ int at(int i, int j) { return j * 20 + i; }
+    static __device__ __forceinline__ void put(float* t, int ln, const acc_t& d) {
+        *(acc_t*)&t[at(row(ln, 0), ln & 15)] = d;
+    }
 };
 
 // Row stride (elements) of the transposes: 64 particles plus padding, so that
@@ -482,6 +615,11 @@ constexpr int fb_xs() { return sizeof(Real) == 4 ? 68 : 66; }
 // reads) before it takes the sixteen of add() (ja2 adjoint: 17.8 ms with add()
 // only, 16.9 ms at 4 or 8, 17.8 ms when it never takes add()).
 constexpr int kFbLiveMax = 8;
+
+// The products q that hold a particle of the wave mask `live` (bit q).
+__device__ __forceinline__ uint32_t fb_live_products(uint64_t live) {
+    return (uint32_t)(live | live >> 16 | live >> 32 | live >> 48) & 0xFFFFu;
+}
 
 template <typename Real, int VR>
 struct FbWave {
@@ -529,7 +667,7 @@ struct FbWave {
     // sum is bitwise that of add().  Pays when few particles are live (a
     // jump-adapted sub-step run for the wave's jumping lanes).
     __device__ __forceinline__ void add_live(uint64_t live) {
-        uint32_t qm = (uint32_t)(live | live >> 16 | live >> 32 | live >> 48) & 0xFFFFu;
+        uint32_t qm = fb_live_products(live);
         if (__builtin_popcount(qm) > kFbLiveMax) {
             add();
             return;
@@ -574,8 +712,6 @@ struct FbShared {
 
 template <typename Real, int VR, int W>
 __device__ __forceinline__ FbWave<Real, VR> fb_wave(FbShared<Real, VR, W>& sh) {
-    static_assert(sizeof(Real) * kFbMaxGrid * fb_xs<Real>() >= sizeof(double) * kFbMaxGrid * kFbMaxGrid,
-                  "a wave's transpose buffer must hold its 16 x 16 FP64 tile");
     FbWave<Real, VR> w;
     const int wv = threadIdx.x >> 6;
     w.phx = sh.phx[wv];
@@ -588,17 +724,18 @@ __device__ __forceinline__ FbWave<Real, VR> fb_wave(FbShared<Real, VR, W>& sh) {
     return w;
 }
 
-// The wave's FP64 16 x 16 tiles of its last H steps (t[0] the latest), in the
-// D layout of the path precision's matrix-core product.  The waves of a block
-// combine their tiles once per H steps: H = 2 for independent particles on
-// the fixed grid (kFbAdjHold), 1 for rings (whose neighbour exchange needs the
-// flush's barriers every step) and the surrogate's forward, 4 for the
-// jump-adapted adjoint (54.9 -> 51.1 ms on ja2).
-template <int H>
+// The wave's 16 x 16 tiles of its last H steps (t[0] the latest), in the
+// registers of the path precision's matrix-core product.  The waves of a block
+// combine their tiles once per H steps: fb_adj_hold() for independent
+// particles, 1 for rings (whose neighbour exchange needs the flush's barriers
+// every step) and the surrogate's forward.  FP32 tiles are held and staged as
+// they are and widened where they are summed (exact): held in FP64 they took
+// twice the registers and LDS.
+template <typename Real, int H>
 struct FbHist {
-    fb_d4 t[H];
+    typename FbMma<Real>::acc_t t[H];
     int cnt;
-    __device__ __forceinline__ void push(const fb_d4& x) {
+    __device__ __forceinline__ void push(const typename FbMma<Real>::acc_t& x) {
 #pragma unroll
         for (int s = H - 1; s > 0; --s)
             t[s] = t[s - 1];
@@ -607,32 +744,24 @@ struct FbHist {
     }
 };
 
-// The wave's sums, in FP64.
-template <typename Real, int VR>
-__device__ __forceinline__ fb_d4 fb_tile(const FbWave<Real, VR>& w) {
-    fb_d4 t;
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-        t[r] = (double)w.acc[r];
-    return t;
-}
-
-// Number of 16 x 16 FP64 tiles a wave's transposes hold: in phx, in phv.
-constexpr int kFbTile = kFbMaxGrid * kFbMaxGrid;
+// Number of tiles a wave's transposes hold: in phx, in phv.
 template <typename Real>
-constexpr int fb_tiles_x() {
-    return (int)(sizeof(Real) * kFbMaxGrid * fb_xs<Real>() / (sizeof(double) * kFbTile));
-}
+constexpr int fb_tiles_x() { return kFbMaxGrid * fb_xs<Real>() / FbMma<Real>::tile; }
 template <typename Real, int VR>
-constexpr int fb_tiles_v() { return (int)(sizeof(Real) * VR * fb_xs<Real>() / (sizeof(double) * kFbTile)); }
+constexpr int fb_tiles_v() { return VR * fb_xs<Real>() / FbMma<Real>::tile; }
+template <typename Real, int VR>
+constexpr int fb_adj_hold(int most) {
+    constexpr int n = fb_tiles_x<Real>() + fb_tiles_v<Real, VR>();
+    return n < most ? n : most;
+}
 
 // LDS home of tile s of wave wv during a flush (the wave's transpose buffers,
 // free between steps).
 template <typename Real, int VR, int W>
-__device__ __forceinline__ double* fb_tile_lds(FbShared<Real, VR, W>& sh, int wv, int s) {
+__device__ __forceinline__ Real* fb_tile_lds(FbShared<Real, VR, W>& sh, int wv, int s) {
     constexpr int TX = fb_tiles_x<Real>();
-    return s < TX ? (double*)&sh.phx[wv][0][0] + s * kFbTile
-                  : (double*)&sh.phv[wv][0][0] + (s - TX) * kFbTile;
+    return s < TX ? &sh.phx[wv][0][0] + s * FbMma<Real>::tile
+                  : &sh.phv[wv][0][0] + (s - TX) * FbMma<Real>::tile;
 }
 
 struct FbNoMid {
@@ -642,33 +771,51 @@ struct FbNoMid {
 // Sums the W waves' held tiles in a fixed order into the block's partials:
 // tile s is step k0 + s dir (ADD: added to what the partial holds).  mid runs
 // between the flush's two barriers (with every wave's LDS writes before the
-// flush visible, and none of the next step's yet).
+// flush visible, and none of the next step's yet).  In the workgroups of more
+// than four waves (rings) the tile is staged widened: the widening is then
+// shared by all lanes instead of following the reads of the few that sum
+// (512 rings of 2000, 200 steps: adjoint 3.48 against 3.51 ms).
 template <bool ADD, int H, typename Real, int VR, int W, typename Mid = FbNoMid>
 __device__ __forceinline__ void fb_hist_flush(FbShared<Real, VR, W>& sh, const FbWave<Real, VR>& w,
-                                              FbHist<H>& h, int k0, int dir, int N, int nx, int nv,
-                                              double* __restrict__ apart, const Mid& mid = Mid()) {
-    static_assert(H <= fb_tiles_x<Real>() + fb_tiles_v<Real, VR>(),
+                                              FbHist<Real, H>& h, int k0, int dir, int N, int nx,
+                                              int nv, double* __restrict__ apart,
+                                              const Mid& mid = Mid()) {
+    constexpr bool WIDE = W > 4;
+    typedef typename std::conditional<WIDE, double, Real>::type T;
+    static_assert(WIDE ? H == 1 && sizeof(sh.phx[0]) >= sizeof(double) * FbMma<double>::tile
+                       : H <= fb_tiles_x<Real>() + fb_tiles_v<Real, VR>(),
                   "a wave's transposes must hold its H tiles");
+    auto home = [&](int wv, int s) {
+        if constexpr (WIDE)
+            return (double*)&sh.phx[wv][0][0];
+        else
+            return fb_tile_lds(sh, wv, s);
+    };
     const int wv = threadIdx.x >> 6;
 #pragma unroll
     for (int s = 0; s < H; ++s) {
         if (s < h.cnt) {
-            double* cb = fb_tile_lds(sh, wv, s);
+            if constexpr (WIDE) {
+                double* cb = home(wv, s);
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                cb[FbMma<Real>::row(w.ln, r) * kFbMaxGrid + w.ii] = h.t[s][r];
+                for (int r = 0; r < 4; ++r)
+                    cb[FbMma<double>::at(FbMma<Real>::row(w.ln, r), w.ii)] = (double)h.t[s][r];
+            } else {
+                FbMma<Real>::put(home(wv, s), w.ln, h.t[s]);
+            }
         }
     }
     __syncthreads();
     const int t = threadIdx.x, i = t >> 4, j = t & 15;
     if (i < nx && j < nv) {
+        const int e = FbMma<T>::at(i, j);
 #pragma unroll
         for (int s = 0; s < H; ++s) {
             if (s < h.cnt) {
-                double sum = fb_tile_lds(sh, 0, s)[t];
+                double sum = (double)home(0, s)[e];
 #pragma unroll
                 for (int q = 1; q < W; ++q)
-                    sum += fb_tile_lds(sh, q, s)[t];
+                    sum += (double)home(q, s)[e];
                 double* dst = apart + ((size_t)blockIdx.x * N + (k0 + s * dir)) * (nx * nv) + i * nv + j;
                 *dst = ADD ? *dst + sum : sum;
             }
@@ -688,9 +835,9 @@ __device__ __forceinline__ void fb_hist_flush(FbShared<Real, VR, W>& sh, const F
 // mom[(k nb + block) 4 + q].
 template <typename Real, int VR, int W>
 __device__ __forceinline__ double* fb_mom_lds(FbShared<Real, VR, W>& sh, int wv) {
-    static_assert(sizeof(Real) * kFbMaxGrid * fb_xs<Real>() >= sizeof(double) * (kFbTile + 4 * 64),
+    static_assert(sizeof(Real) * kFbMaxGrid * fb_xs<Real>() >= sizeof(Real) * FbMma<Real>::tile + sizeof(double) * 4 * 64,
                   "a wave's position transpose must hold its flush tile and its moments");
-    return (double*)&sh.phx[wv][0][0] + kFbTile;
+    return (double*)(&sh.phx[wv][0][0] + FbMma<Real>::tile);
 }
 template <typename Real, int VR, int W, int G>
 __device__ __forceinline__ void fb_mom_put(FbShared<Real, VR, W>& sh, const Real (&x)[G],

@@ -12,7 +12,7 @@
 //                      on the matrix cores of the path precision
 //  k_fb_forward_grad   the surrogate gradient's forward: forward sweep plus
 //                      the control term of the gradient, nothing stored
-//  k_fb_forward_adapted, k_fb_adjoint_adapted
+//  k_fb_forward_adapted, k_fb_adjoint_adapted, k_fb_adjoint_adapted_rows
 //                      the same on the jump-adapted grid (sub-steps between
 //                      each particle's jump times, a stack of post-jump states)
 //  k_fb_finalize_grad  fixed-order FP64 sum of the per-block gradient partials
@@ -159,7 +159,7 @@ k_fb_forward_grad(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
     __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
     __shared__ double red[kThreads];
     auto wave = fb_wave(sh);
-    FbHist<1> hist;
+    FbHist<Real, 1> hist;
     hist.cnt = 0;
     const int N = a.N;
     Real x[G], v[G], cx[G], cv[G];
@@ -196,7 +196,7 @@ k_fb_forward_grad(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
             acc[j] += (double)(a.dt * track(a, x[j], v[j], zd + 2 * (k + 1)));
             fb_dump(a, a.dX, k + 1, m[j], x[j], v[j]);
         }
-        hist.push(fb_tile(wave));
+        hist.push(wave.acc);
         if (a.mom != nullptr)
             fb_mom_put(sh, x, v, act, zd + 2 * (k + 1));
         fb_hist_flush<false>(sh, wave, hist, k, -1, N, a.nx, a.nv, apart,
@@ -271,8 +271,8 @@ k_fb_adjoint(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict
     __shared__ Real cw[RING ? 2 : 1][RING ? G * TPB : 1];
     auto wave = fb_wave(sh);
     // rings flush every step: the flush's barriers order the neighbour exchange
-    constexpr int H = RING ? 1 : kFbAdjHold;
-    FbHist<H> hist;
+    constexpr int H = RING ? 1 : fb_adj_hold<Real, NVP>(kFbAdjHold);
+    FbHist<Real, H> hist;
     hist.cnt = 0;
     const int N = a.N;
     FbAdj<Real> s[G];
@@ -383,7 +383,7 @@ k_fb_adjoint(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict
                     fb_dump(a, a.dlam, k, m[j], st.lx, st.lv);
             }
         }
-        hist.push(fb_tile(wave));
+        hist.push(wave.acc);
         if (hist.cnt == H || k == 0)
             fb_hist_flush<SURR>(sh, wave, hist, k, 1, N, a.nx, a.nv, apart);
         if (RING && k >= 1) {
@@ -516,6 +516,14 @@ k_fb_forward_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
         cpart[blockIdx.x] = s;
 }
 
+// Whether a particle of this block has more jumps than its stack holds
+// (block-uniform; every thread calls it).
+template <typename Real>
+__device__ __forceinline__ bool fb_past_stack(const void* traj, int N, int64_t nblk) {
+    const FbJumps<Real> j = fb_jumps<Real>(const_cast<void*>(traj), N, nblk);
+    return __syncthreads_or(*j.count > kFbJumpCap) != 0;
+}
+
 // Backward sweep on the jump-adapted grid, one particle per lane.  The lane
 // carries lam~, the adjoint of the interval's end state without the running
 // cost charged there, and the unweighted cost gradient at that state; the
@@ -531,13 +539,15 @@ k_fb_forward_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
 template <typename Real, int NVP>
 __global__ void __launch_bounds__(kThreads, (sizeof(Real) == 4 ? 4 : 2))
 k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
-                     const void* traj, double* __restrict__ apart) {
+                     const void* traj, double* __restrict__ apart, bool past_stack) {
     if (gate_closed(a.gate))
         return;
-    // four held tiles: FP32 needs all 16 velocity rows for them
-    __shared__ FbShared<Real, sizeof(Real) == 4 ? kFbMaxGrid : fb_vrows<NVP>()> sh;
+    if (past_stack && !fb_past_stack<Real>(traj, a.N, a.nblk))
+        return;
+    __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
     auto wave = fb_wave(sh);
-    FbHist<4> hist;
+    constexpr int H = fb_adj_hold<Real, NVP>(4);
+    FbHist<Real, H> hist;
     hist.cnt = 0;
     const int N = a.N;
     const FbSlot sl = fb_slot<1>(a, 0);
@@ -699,8 +709,213 @@ k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
         }
         jend = jb;
         track_grad(a, xk, vk, zk, gxe, gve);
-        hist.push(fb_tile(wave));
-        if (hist.cnt == 4 || k == 0)
+        hist.push(wave.acc);
+        if (hist.cnt == H || k == 0)
+            fb_hist_flush<false>(sh, wave, hist, k, 1, N, a.nx, a.nv, apart);
+        xk = xp;
+        vk = vp;
+    }
+}
+
+// The same sweep where few particles jump in an interval (fb_row_jumps) and every
+// jump is on the stack (blocks with a particle past it return and are left to
+// k_fb_adjoint_adapted).  A sub-step after a jump belongs to few of the wave's
+// particles (ja2: 1.1 per interval); evaluated in every lane it doubled the
+// kernel's work (1022 VALU instructions per interval against 512).  Here the
+// sub-steps r >= 1 are evaluated by rows of 16 lanes: the matrix-core product q
+// takes particles 16 kk + q, so row kk evaluates that particle, lane j its shape
+// functions j, and the lanes' values are the product's operands as they stand
+// (no LDS transposes).  The operations, and the products in their order, are
+// k_fb_adjoint_adapted's (whose products with no live particle add zeros).
+// ja2 adjoint: FP32 15.4 -> 11.5 ms (0.73 of it the fixed grid's 8.4 ms), at four
+// waves per SIMD (five spill: 13.0 ms); 2^18 FP64 particles 12.05 -> 7.35 ms.
+template <typename Real, int NVP>
+__global__ void __launch_bounds__(kThreads, (sizeof(Real) == 4 ? 4 : 2))
+k_fb_adjoint_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
+                          const Real* __restrict__ zd, const void* traj,
+                          double* __restrict__ apart) {
+    if (gate_closed(a.gate))
+        return;
+    if (fb_past_stack<Real>(traj, a.N, a.nblk))
+        return;
+    __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
+    auto wave = fb_wave(sh);
+    constexpr int H = fb_adj_hold<Real, NVP>(4);
+    FbHist<Real, H> hist;
+    hist.cnt = 0;
+    const int N = a.N;
+    const FbSlot sl = fb_slot<1>(a, 0);
+    // the interval's control rows for the row evaluation, loaded an interval
+    // ahead and put in the wave's LDS when an interval needs them
+    constexpr int NM = (kFbMaxGrid * NVP + 63) / 64;
+    __shared__ Real mrow[kFbWaves][kFbMaxGrid * NVP];
+    Real* const mw = mrow[threadIdx.x >> 6];
+    const int ln = threadIdx.x & 63, lj = ln & 15;
+    const int nm = a.nx * NVP;
+    Real pm[NM];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            const int e = q * 64 + ln;
+            pm[q] = mu[(size_t)k * nm + (e < nm ? e : 0)];
+        }
+    };
+    fetch(N - 1);
+    const Real* row = fb_row<Real>(const_cast<void*>(traj), N, blockIdx.x);
+    const FbJumps<Real> jumps = fb_jumps<Real>(const_cast<void*>(traj), N, a.nblk);
+    int jend = *jumps.count;  // jumps in the intervals up to the current one
+    int nk = __builtin_nontemporal_load(jumps.per + (size_t)(N - 1) * kThreads);
+    int nk2 = N >= 2 ? __builtin_nontemporal_load(jumps.per + (size_t)(N - 2) * kThreads) : 0;
+    // the stack entry of each interval's first jump, loaded an interval ahead
+    Real pfx = 0, pfv = 0, pfa = 0;
+    fb_stack_entry(jumps, jend - nk, nk > 0, pfx, pfv, pfa);
+    Real gxe, gve;  // unweighted running-cost gradient at the interval's end state
+    {
+        const Real xN = __builtin_nontemporal_load(row + (size_t)N * 2 * kThreads);
+        const Real vN = __builtin_nontemporal_load(row + (size_t)N * 2 * kThreads + kThreads);
+        track_grad(a, xN, vN, zd + 2 * N, gxe, gve);
+    }
+    Real lx = 0, lv = 0;
+    Real xk = __builtin_nontemporal_load(row + (size_t)(N - 1) * 2 * kThreads);
+    Real vk = __builtin_nontemporal_load(row + (size_t)(N - 1) * 2 * kThreads + kThreads);
+    for (int k = N - 1; k >= 0; --k) {
+        const Real* mk = mu + (size_t)k * nm;
+        const Real* zk = zd + 2 * k;
+        Real xp = 0, vp = 0;
+        if (k >= 1) {
+            xp = __builtin_nontemporal_load(row + (size_t)(k - 1) * 2 * kThreads);
+            vp = __builtin_nontemporal_load(row + (size_t)(k - 1) * 2 * kThreads + kThreads);
+        }
+        const int n = nk;
+        nk = nk2;
+        if (k >= 2)
+            nk2 = __builtin_nontemporal_load(jumps.per + (size_t)(k - 2) * kThreads);
+        const int jb = jend - n;  // stack entry of this interval's first jump
+        const Real e0x = pfx, e0v = pfv, e0a = pfa;
+        if (k >= 1)
+            fb_stack_entry(jumps, jb - nk, nk > 0, pfx, pfv, pfa);
+        int nmax = 0;
+        while (__builtin_amdgcn_ballot_w64(n > nmax))
+            ++nmax;
+        Real m[NVP];  // lane j: control row j (zeros past the grid)
+        if (nmax > 0) {
+            wave_lds_sync();
+#pragma unroll
+            for (int q = 0; q < NM; ++q)
+                if (q * 64 + ln < nm)
+                    mw[q * 64 + ln] = pm[q];
+            wave_lds_sync();
+#pragma unroll
+            for (int l = 0; l < NVP; ++l)
+                m[l] = lj < a.nx ? mw[lj * NVP + l] : (Real)0;
+        }
+        if (k >= 1)
+            fetch(k - 1);
+        wave.clear();
+        // sub-steps r = n .. 1; (sx, sv, sa): the start of the sub-step after the
+        // one at hand, which is the state after the jump that ends it
+        Real sx = 0, sv = 0, sa = 1;
+        for (int r = nmax; r >= 1; --r) {
+            const bool mine = r <= n;
+            Real x = e0x, v = e0v, a0 = e0a;
+            if (r > 1)
+                fb_stack_entry(jumps, jb + r - 1, mine, x, v, a0);
+            const Real d = (sa - a0) * a.dt;
+            if (mine) {
+                Real gx = gxe, gv = gve;
+                if (r < n) {
+                    Real tg[2];
+                    fb_target(zk, sa, tg);
+                    track_grad(a, sx, sv, tg, gx, gv);
+                }
+                lx = fma(d, gx, lx);
+                lv = fma(d, gv, lv);
+                if (r == n && sl.act)
+                    fb_dump(a, a.dlam, k + 1, sl.p, lx, lv);
+            }
+            const Real lvm = r < n ? a.gamma * lv : lv;
+            const Real share = sa - a0;  // the sub-step's share d / dt of the step
+            const uint64_t live = __builtin_amdgcn_ballot_w64(mine && sl.act);
+            uint32_t qm = fb_live_products(live);
+            Real u = 0, ux = 0, uv = 0;
+            while (qm != 0) {
+                const int q = __builtin_ctz(qm);
+                qm &= qm - 1;
+                const int src = (ln & 48) | q;
+                const Real xq = __shfl(x, src), vq = __shfl(v, src);
+                const Real lq = __shfl(lvm, src), sq = __shfl(share, src);
+                Real bx, pv, uq, uxq, uvq;
+                if (a.nx <= 10)
+                    row_control_grad<Real, NVP, 10>(a, m, lj, xq, vq, bx, pv, uq, uxq, uvq);
+                else
+                    row_control_grad<Real, NVP, 16>(a, m, lj, xq, vq, bx, pv, uq, uxq, uvq);
+                const Real wk = sq * fma(a.alpha, uq, lq);
+                wave.acc = FbMma<Real>::mfma(bx, pv * ((live >> src) & 1 ? wk : (Real)0),
+                                             wave.acc);
+                if (lj == q) {
+                    u = uq;
+                    ux = uxq;
+                    uv = uvq;
+                }
+            }
+            if (mine) {
+                const Real au = a.alpha * u;
+                const Real lxm = lx;
+                lx = fma(d, fma(au, ux, (ux - a.eta) * lvm), lxm);
+                lv = fma(d, fma(au, uv, fma(uv, lvm, lxm)), lvm);
+                sx = x;
+                sv = v;
+                sa = a0;
+            }
+        }
+        // sub-step 0, every lane
+        const Real d = n == 0 ? a.dt : sa * a.dt;
+        {
+            Real gx = gxe, gv = gve;
+            if (n > 0) {
+                Real tg[2];
+                fb_target(zk, sa, tg);
+                track_grad(a, sx, sv, tg, gx, gv);
+            }
+            lx = fma(d, gx, lx);
+            lv = fma(d, gv, lv);
+            if (n == 0 && sl.act)
+                fb_dump(a, a.dlam, k + 1, sl.p, lx, lv);
+        }
+        const Real lxm = lx, lvm = n > 0 ? a.gamma * lv : lv;
+        Real pv[NVP], dpv[NVP];
+#pragma unroll
+        for (int l = 0; l < NVP; ++l)
+            pv[l] = bump_dq(fma(-(Real)l, a.eps * a.dvc, a.eps * (vk - a.vc0)), dpv[l]);
+        Real u = 0, ux = 0, uv = 0;
+#pragma unroll 2
+        for (int i = 0; i < a.nx; ++i) {
+            Real dbx;
+            const Real bx = bump_dq(fma(-(Real)i, a.eps * a.dxc, a.eps * (xk - a.xc0)), dbx);
+            const Real* rw = mk + i * NVP;
+            Real t = 0, st = 0;
+#pragma unroll
+            for (int l = 0; l < NVP; ++l) {
+                t = fma(rw[l], pv[l], t);
+                st = fma(rw[l], dpv[l], st);
+            }
+            u = fma(bx, t, u);
+            ux = fma(dbx, t, ux);
+            uv = fma(bx, st, uv);
+            wave.put_x(i, bx);
+        }
+        ux *= (Real)-2 * a.eps;  // d carries b'(r) / (-2 eps)
+        uv *= (Real)-2 * a.eps;
+        const Real wk = n == 0 ? fma(a.alpha, u, lvm) : sa * fma(a.alpha, u, lvm);
+        wave.template put_vw<Real, NVP>(pv, sl.act ? wk : (Real)0);
+        wave.add_live(__builtin_amdgcn_ballot_w64(sl.act));
+        const Real au = a.alpha * u;
+        lx = fma(d, fma(au, ux, (ux - a.eta) * lvm), lxm);
+        lv = fma(d, fma(au, uv, fma(uv, lvm, lxm)), lvm);
+        jend = jb;
+        track_grad(a, xk, vk, zk, gxe, gve);
+        hist.push(wave.acc);
+        if (hist.cnt == H || k == 0)
             fb_hist_flush<false>(sh, wave, hist, k, 1, N, a.nx, a.nv, apart);
         xk = xp;
         vk = vp;
@@ -975,6 +1190,15 @@ hipError_t fb_launch_forward(const FbHost& p, const HostRun& r, const void* tab,
                              : fb_forward_t<float>(p, r, tab, traj, cpart, hdr, st, gate);
 }
 
+// Jumps per particle and interval up to which the jump-adapted adjoint evaluates
+// the sub-steps after a jump in rows: with more of them a pass over the whole
+// wave costs less than one row evaluation per product.  Rows / whole wave on 2^20
+// FP32 particles: 11.5 / 15.4 ms at 0.018 (500 steps), 5.87 / 7.10 at 0.045, 3.87 / 4.08
+// at 0.089, 3.26 / 3.19 at 0.127, 2.77 / 2.53 at 0.18; on 2^18 FP64 particles: 7.35 /
+// 12.05 at 0.018, 2.19 / 3.08 at 0.089, 1.13 / 1.30 at 0.30, 0.94 / 1.00 at 0.45.
+template <typename Real>
+constexpr double fb_row_jumps() { return sizeof(Real) == 4 ? 0.1 : 0.45; }
+
 template <typename Real>
 static hipError_t fb_adjoint_t(const FbHost& p, const HostRun& r, const void* tab, const void* traj,
                                double* apart, const WsHeader* hdr, bool surr, hipStream_t st,
@@ -996,8 +1220,12 @@ static hipError_t fb_adjoint_t(const FbHost& p, const HostRun& r, const void* ta
 #define FB_ADJ(NVP)                                                                               \
     do {                                                                                          \
         if (p.grid == 1) {                                                                        \
+            const bool rows = p.rate * p.dt <= fb_row_jumps<Real>();                                       \
+            if (rows)                                                                             \
+                hipLaunchKernelGGL((k_fb_adjoint_adapted_rows<Real, NVP>), dim3(nb),              \
+                                   dim3(kThreads), 0, st, a, tb + t.mu, tb + t.zd, traj, apart);  \
             hipLaunchKernelGGL((k_fb_adjoint_adapted<Real, NVP>), dim3(nb), dim3(kThreads), 0,    \
-                               st, a, tb + t.mu, tb + t.zd, traj, apart);                         \
+                               st, a, tb + t.mu, tb + t.zd, traj, apart, rows);                   \
         } else if (p.np > 1) {                                                                    \
             if (G == 8) {                                                                         \
                 constexpr int RT = fb_ring_adj_threads<Real, NVP>();                              \

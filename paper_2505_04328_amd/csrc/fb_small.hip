@@ -30,39 +30,6 @@
 namespace jd {
 
 // ---------------------------------------------------------------------------
-// Row broadcasts: lane I of the caller's row of 16 lanes (DPP row_newbcast).
-template <int I>
-__device__ __forceinline__ float row_bcast(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(
-        0, __builtin_bit_cast(int, v), 0x150 + I, 0xf, 0xf, true));
-}
-template <int I>
-__device__ __forceinline__ double row_bcast(double v) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x150 + I, 0xf,
-                                                              0xf, true);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32),
-                                                              0x150 + I, 0xf, 0xf, true);
-    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
-}
-
-// t <- fma(m[l], pv of lane l, t) for l = I .. W-1, in that order.
-template <typename Real, int W, int I = 0>
-__device__ __forceinline__ Real row_dot(const Real (&m)[W], Real pv, Real t) {
-    if constexpr (I < W)
-        return row_dot<Real, W, I + 1>(m, pv, fma(m[I], row_bcast<I>(pv), t));
-    else
-        return t;
-}
-// u <- fma(b of lane i, t of lane i, u) for i = I .. W-1, in that order.
-template <typename Real, int W, int I = 0>
-__device__ __forceinline__ Real row_sum(Real b, Real t, Real u) {
-    if constexpr (I < W)
-        return row_sum<Real, W, I + 1>(b, t, fma(row_bcast<I>(b), row_bcast<I>(t), u));
-    else
-        return u;
-}
-
 // The feedback control of the row's particle at (x, v), as fb_control: lane j
 // holds row j of the step's coefficients in m (zeros past the grid; a zero
 // term leaves a sum as it is).
@@ -72,7 +39,7 @@ __device__ __forceinline__ Real row_control(const FbArgs<Real>& a, const Real (&
     const Real bx = bump_q(fma(-(Real)j, a.eps * a.dxc, a.eps * (x - a.xc0)));
     const Real pv = bump_q(fma(-(Real)j, a.eps * a.dvc, a.eps * (v - a.vc0)));
     const Real t = row_dot<Real, W>(m, pv, (Real)0);
-    return row_sum<Real, W>(bx, t, (Real)0);
+    return row_sum<Real, W>(bx, t);
 }
 
 // Draws of one step: the Box-Muller cosine and sine branches, the jump normal
@@ -592,9 +559,9 @@ k_fb_contract(FbArgs<Real> a, const void* traj, const Real* __restrict__ wgt,
         wave.template put_vw<Real, NVP>(pv, w);
         wave.add();
     }
-    FbHist<1> hist;
+    FbHist<Real, 1> hist;
     hist.cnt = 0;
-    hist.push(fb_tile(wave));
+    hist.push(wave.acc);
     // the flush writes partial column blockIdx.x of one step: column
     // (col N + k) as the block, step 0 of 1
     fb_hist_flush<false>(sh, wave, hist, 0, 1, 1, a.nx, a.nv, apart);
