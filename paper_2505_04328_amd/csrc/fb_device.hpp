@@ -38,6 +38,7 @@ struct FbArgs {
     uint32_t key0, key1, iter;
     const PoissonTable* thr;  // in the workspace header, then in the block's LDS
     uint32_t thr0;            // thr->tm1[0], read once per block
+    const DrawTable* dtab;    // the block's LDS copy of the draw table (FP64; set in the kernel)
     Gate gate;  // launch gate (word null: always runs)
     double dt64;
     int64_t dm0, dcount;  // per-path dumps
@@ -130,18 +131,18 @@ __device__ __forceinline__ void fb_initial(const FbArgs<Real>& a, uint32_t m, Re
     uint32_t w[4];
     philox4x32_10<true>(m, kFbInitStep, a.iter, 0u, a.key0, a.key1, w);
     if (a.init_kind == 0) {
-        const Real R = bm_radius(w[0], (Real)0);
-        const Real ub = unit_uniform<Real>(w[1]);
-        x = fma(a.s0x, bm_cos(R, ub), a.z0x);
-        v = fma(a.s0v, bm_sin(R, ub), a.z0v);
+        const Real R = bm_radius(w[0], (Real)0, a.dtab);
+        const auto ub = bm_angle<Real>(w[1]);
+        x = fma(a.s0x, bm_cos(R, ub, a.dtab), a.z0x);
+        v = fma(a.s0v, bm_sin(R, ub, a.dtab), a.z0v);
     } else if (a.init_kind == 2) {
         // particle j = m mod np of its ring at angle 2 pi j / np on the ellipse
         double sn, cs;
         sincospi(2.0 * (double)(m % (uint32_t)a.np) / (double)a.np, &sn, &cs);
-        const Real R = bm_radius(w[0], (Real)0);
-        const Real ub = unit_uniform<Real>(w[1]);
-        x = fma(a.s0x, bm_cos(R, ub), (Real)((double)a.ax * cs));
-        v = fma(a.s0v, bm_sin(R, ub), (Real)((double)a.av * sn));
+        const Real R = bm_radius(w[0], (Real)0, a.dtab);
+        const auto ub = bm_angle<Real>(w[1]);
+        x = fma(a.s0x, bm_cos(R, ub, a.dtab), (Real)((double)a.ax * cs));
+        v = fma(a.s0v, bm_sin(R, ub, a.dtab), (Real)((double)a.av * sn));
     } else {
         x = fma(a.s0x, fma((Real)2, unit_uniform<Real>(w[0]), (Real)-1), a.z0x);
         v = fma(a.s0v, fma((Real)2, unit_uniform<Real>(w[1]), (Real)-1), a.z0v);
@@ -389,23 +390,23 @@ __device__ __forceinline__ Real fb_step(const FbArgs<Real>& a, const Real* __res
     const Real u = fb_control<Real, NVP, Sink, RU>(a, mk, x, v, sink);
     uint32_t w[4];
     philox4x32_10<true>(m, (uint32_t)k, a.iter, 0u, a.key0, a.key1, w);
-    const Real R = bm_radius(w[0], (Real)0);
-    const Real ub = unit_uniform<Real>(w[1]);
+    const Real R = bm_radius(w[0], (Real)0, a.dtab);
+    const auto ub = bm_angle<Real>(w[1]);
     const int n = poisson_count(poisson_word(w), a.thr0, a.thr);
     if (n_out != nullptr)
         *n_out = n;
     Real xn, vs, ex = 0, ev = 0;
     if constexpr (sizeof(Real) == 4) {
-        xn = two_sum(x, fma(a.dt, v, fma(a.sqb1, bm_cos(R, ub), cx)), ex);
-        vs = two_sum(v, fma(a.dt, fma(-a.eta, x, u) - cpl, fma(a.sqb2, bm_sin(R, ub), cv)), ev);
+        xn = two_sum(x, fma(a.dt, v, fma(a.sqb1, bm_cos(R, ub, a.dtab), cx)), ex);
+        vs = two_sum(v, fma(a.dt, fma(-a.eta, x, u) - cpl, fma(a.sqb2, bm_sin(R, ub, a.dtab), cv)), ev);
     } else {
-        xn = fma(a.sqb1, bm_cos(R, ub), fma(a.dt, v, x));
-        vs = fma(a.sqb2, bm_sin(R, ub), fma(a.dt, fma(-a.eta, x, u) - cpl, v));
+        xn = fma(a.sqb1, bm_cos(R, ub, a.dtab), fma(a.dt, v, x));
+        vs = fma(a.sqb2, bm_sin(R, ub, a.dtab), fma(a.dt, fma(-a.eta, x, u) - cpl, v));
     }
     if (__builtin_amdgcn_ballot_w64(n != 0)) {
         Real gn, sv;
         ks_factors(ks, n, gn, sv);
-        const Real zj = bm_cos(bm_radius(w[2], (Real)0), unit_uniform<Real>(w[3]));
+        const Real zj = bm_cos(bm_radius(w[2], (Real)0, a.dtab), bm_angle<Real>(w[3]), a.dtab);
         const Real vj = fma(sv, zj, gn * vs);
         vs = n != 0 ? vj : vs;
         ev = n != 0 ? gn * ev : ev;
@@ -426,10 +427,10 @@ __device__ __forceinline__ void fb_surrogate_sample(const FbArgs<Real>& a, uint3
                                                     Real& cv) {
     uint32_t w[4];
     philox4x32_10<true>(m, kFbSurrWord, a.iter, 1u, a.key0, a.key1, w);
-    const Real R = bm_radius(w[0], (Real)0);
-    const Real ub = unit_uniform<Real>(w[1]);
-    cx = bm_cos(R, ub);
-    cv = bm_sin(R, ub);
+    const Real R = bm_radius(w[0], (Real)0, a.dtab);
+    const auto ub = bm_angle<Real>(w[1]);
+    cx = bm_cos(R, ub, a.dtab);
+    cv = bm_sin(R, ub, a.dtab);
 }
 template <typename Real>
 __device__ __forceinline__ void fb_surrogate(const FbArgs<Real>& a, const Real* __restrict__ zd,
@@ -900,7 +901,9 @@ struct FbMomMid {
 __device__ __forceinline__ float fb_root(float V, int c) {
     return __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(V) / (float)c);
 }
-__device__ __forceinline__ double fb_root(double V, int c) { return pow(V, 1.0 / (double)c); }
+__device__ __forceinline__ double fb_root(double V, int c) {
+    return c == 1 ? V : pow(V, 1.0 / (double)c);  // one jump left: most intervals with a jump
+}
 
 // a_{r+1} from a_r: the smallest of the n - r uniforms left on (a_r, 1), with
 // V_{r+1} = word r mod 4 of block (m, k, iter, 64 + r / 4).
@@ -1000,13 +1003,13 @@ __device__ __forceinline__ void fb_advance(const FbArgs<Real>& a, const Real* __
         if (r < n) {
             uint32_t w[4];
             philox4x32_10<false>(m, (uint32_t)k, a.iter, (uint32_t)(r + 1), a.key0, a.key1, w);
-            const Real S = bm_cos(bm_radius(w[2], (Real)0), unit_uniform<Real>(w[3]));
+            const Real S = bm_cos(bm_radius(w[2], (Real)0, a.dtab), bm_angle<Real>(w[3]), a.dtab);
             v = fma(S, a.sbeta, a.gamma * v);
             cv = a.gamma * cv;
-            const Real R = bm_radius(w[0], (Real)0);
-            const Real ub = unit_uniform<Real>(w[1]);
-            zx = bm_cos(R, ub);
-            zv = bm_sin(R, ub);
+            const Real R = bm_radius(w[0], (Real)0, a.dtab);
+            const auto ub = bm_angle<Real>(w[1]);
+            zx = bm_cos(R, ub, a.dtab);
+            zv = bm_sin(R, ub, a.dtab);
             if (jumps != nullptr) {
                 if (*nj < kFbJumpCap) {
                     jumps->st[(size_t)(kFbJumpComp * *nj) * kThreads] = x;
@@ -1032,10 +1035,10 @@ __device__ __forceinline__ void fb_interval_normals(const FbArgs<Real>& a, uint3
                                                     Real& zx, Real& zv) {
     uint32_t w[4];
     philox4x32_10<true>(m, (uint32_t)k, a.iter, 0u, a.key0, a.key1, w);
-    const Real R = bm_radius(w[0], (Real)0);
-    const Real ub = unit_uniform<Real>(w[1]);
-    zx = bm_cos(R, ub);
-    zv = bm_sin(R, ub);
+    const Real R = bm_radius(w[0], (Real)0, a.dtab);
+    const auto ub = bm_angle<Real>(w[1]);
+    zx = bm_cos(R, ub, a.dtab);
+    zv = bm_sin(R, ub, a.dtab);
 }
 
 // The count and sub-step-0 normals of interval k, and a_1.
@@ -1045,10 +1048,10 @@ __device__ __forceinline__ int fb_interval(const FbArgs<Real>& a, uint32_t m, in
     uint32_t w[4];
     philox4x32_10<true>(m, (uint32_t)k, a.iter, 0u, a.key0, a.key1, w);
     const int n = poisson_count(poisson_word(w), a.thr0, a.thr);
-    const Real R = bm_radius(w[0], (Real)0);
-    const Real ub = unit_uniform<Real>(w[1]);
-    zx = bm_cos(R, ub);
-    zv = bm_sin(R, ub);
+    const Real R = bm_radius(w[0], (Real)0, a.dtab);
+    const auto ub = bm_angle<Real>(w[1]);
+    zx = bm_cos(R, ub, a.dtab);
+    zv = bm_sin(R, ub, a.dtab);
     a1 = n > 0 ? fb_next_offset(a, m, k, 0, n, (Real)0) : (Real)1;
     return n;
 }
@@ -1112,6 +1115,7 @@ static FbArgs<Real> fb_args(const FbHost& p, const HostRun& r) {
     a.iter = r.iter;
     a.thr = nullptr;
     a.thr0 = 0;
+    a.dtab = nullptr;
     a.gate = kNoGate;
     a.dt64 = p.dt;
     a.dm0 = 0;

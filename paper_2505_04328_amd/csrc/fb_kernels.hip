@@ -74,6 +74,8 @@ k_fb_forward(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict
     fb_stage_thresholds(a, &thr);
     __shared__ Real ks_lds[64];
     ks = fb_stage_ks(ks, ks_lds);
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
     static_assert(RING || (G == 1 && TPB == kThreads), "independent particles run one per lane");
     __shared__ double sh[TPB];
     __shared__ Real xs[RING ? 2 : 1][RING ? G * TPB : 1];
@@ -156,6 +158,8 @@ k_fb_forward_grad(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
     fb_stage_thresholds(a, &thr);
     __shared__ Real ks_lds[64];
     ks = fb_stage_ks(ks, ks_lds);
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
     __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
     __shared__ double red[kThreads];
     auto wave = fb_wave(sh);
@@ -265,6 +269,10 @@ k_fb_adjoint(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict
         fb_stage_thresholds(a, &thr);
     __shared__ Real ks_lds[64];
     ks = fb_stage_ks(ks, ks_lds);
+    if constexpr (SURR) {
+        __shared__ DrawLds<Real> dl;
+        a.dtab = dl.stage();
+    }
     static_assert(!(SURR && RING), "the surrogate gradient takes independent particles");
     static_assert(RING || TPB == kThreads, "independent particles run in blocks of 256");
     __shared__ FbShared<Real, fb_vrows<NVP>(), TPB / 64> sh;
@@ -412,6 +420,8 @@ k_fb_forward_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
         return;
     __shared__ PoissonTable thr;
     fb_stage_thresholds(a, &thr);
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
     __shared__ double sh[kThreads];
     const FbSlot sl = fb_slot<1>(a, 0);
     Real x, v, cx = 0, cv = 0;
@@ -455,13 +465,13 @@ k_fb_forward_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
                 uint32_t w[4];
                 philox4x32_10<false>(sl.p, (uint32_t)k, a.iter, (uint32_t)(r + 1), a.key0, a.key1,
                                      w);
-                const Real S = bm_cos(bm_radius(w[2], (Real)0), unit_uniform<Real>(w[3]));
+                const Real S = bm_cos(bm_radius(w[2], (Real)0, a.dtab), bm_angle<Real>(w[3]), a.dtab);
                 v = fma(S, a.sbeta, a.gamma * v);
                 cv = a.gamma * cv;
-                const Real R = bm_radius(w[0], (Real)0);
-                const Real ub = unit_uniform<Real>(w[1]);
-                zx = bm_cos(R, ub);
-                zv = bm_sin(R, ub);
+                const Real R = bm_radius(w[0], (Real)0, a.dtab);
+                const auto ub = bm_angle<Real>(w[1]);
+                zx = bm_cos(R, ub, a.dtab);
+                zv = bm_sin(R, ub, a.dtab);
                 if (STORE) {
                     if (nj < kFbJumpCap) {
                         jumps.st[(size_t)(kFbJumpComp * nj) * kThreads] = x;
@@ -544,6 +554,8 @@ k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
         return;
     if (past_stack && !fb_past_stack<Real>(traj, a.N, a.nblk))
         return;
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
     __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
     auto wave = fb_wave(sh);
     constexpr int H = fb_adj_hold<Real, NVP>(4);
@@ -1006,6 +1018,8 @@ k_fb_draws(FbArgs<Real> a, PoissonTable pt, int64_t m0, int64_t mc, int k0, int 
     __syncthreads();
     a.thr = &tb;
     a.thr0 = tb.tm1[0];
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
     const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (idx >= mc * kc)
         return;
@@ -1020,12 +1034,12 @@ k_fb_draws(FbArgs<Real> a, PoissonTable pt, int64_t m0, int64_t mc, int k0, int 
     }
     uint32_t w[4];
     philox4x32_10<false>(m, (uint32_t)(k0 + q), a.iter, 0u, a.key0, a.key1, w);
-    const Real R = bm_radius(w[0], (Real)0);
-    const Real ub = unit_uniform<Real>(w[1]);
+    const Real R = bm_radius(w[0], (Real)0, a.dtab);
+    const auto ub = bm_angle<Real>(w[1]);
     if (Z != nullptr) {
-        Z[3 * idx] = bm_cos(R, ub);
-        Z[3 * idx + 1] = bm_sin(R, ub);
-        Z[3 * idx + 2] = bm_cos(bm_radius(w[2], (Real)0), unit_uniform<Real>(w[3]));
+        Z[3 * idx] = bm_cos(R, ub, a.dtab);
+        Z[3 * idx + 1] = bm_sin(R, ub, a.dtab);
+        Z[3 * idx + 2] = bm_cos(bm_radius(w[2], (Real)0, a.dtab), bm_angle<Real>(w[3]), a.dtab);
     }
     if (counts != nullptr)
         counts[idx] = poisson_count(poisson_word(w), a.thr0, a.thr);

@@ -127,6 +127,8 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
     fb_stage_thresholds(a, &thr);
     __shared__ Real ks_lds[64];
     ks = fb_stage_ks(ks, ks_lds);
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
     __shared__ alignas(16) Real mus[16][W][WS];
     __shared__ FbRowDraw<Real> dr[SL][17];
     __shared__ Real xs[RING ? 2 : 1][RING ? SL : 1];
@@ -203,15 +205,15 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
             // lane j: the draws of step kb + j
             uint32_t w[4];
             philox4x32_10<false>((uint32_t)p, (uint32_t)(kb + j), a.iter, 0u, a.key0, a.key1, w);
-            const Real R = bm_radius(w[0], (Real)0);
-            const Real ub = unit_uniform<Real>(w[1]);
+            const Real R = bm_radius(w[0], (Real)0, a.dtab);
+            const auto ub = bm_angle<Real>(w[1]);
             FbRowDraw<Real> d;
-            d.zc = bm_cos(R, ub);
-            d.zs = bm_sin(R, ub);
+            d.zc = bm_cos(R, ub, a.dtab);
+            d.zs = bm_sin(R, ub, a.dtab);
             d.zj = 0;
             const int n = poisson_count(poisson_word(w), a.thr0, a.thr);
             if (n != 0)
-                d.zj = bm_cos(bm_radius(w[2], (Real)0), unit_uniform<Real>(w[3]));
+                d.zj = bm_cos(bm_radius(w[2], (Real)0, a.dtab), bm_angle<Real>(w[3]), a.dtab);
             d.n = (Real)n;
             dr[row][j] = d;
         }

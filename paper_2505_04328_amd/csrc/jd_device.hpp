@@ -8,6 +8,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "jd_draw_table.hpp"
 #include "jd_launch.hpp"
 
 namespace jd {
@@ -94,17 +95,124 @@ __device__ __forceinline__ Real unit_uniform(uint32_t w) {
 // one instruction.  The uniforms are never 0, denormal or 1, so no range
 // handling is needed; the result matches the FP64 transform to within 1e-6
 // absolute, like the correctly-rounded library functions.
-__device__ __forceinline__ float bm_radius(uint32_t a, float) {
+__device__ __forceinline__ float bm_radius(uint32_t a, float, const DrawTable*) {
     const float l2 = __builtin_amdgcn_logf(unit_uniform<float>(a));  // log2(u_a)
     return __builtin_amdgcn_sqrtf(-1.38629436111989061883f * l2);    // sqrt(-2 ln u_a)
 }
-__device__ __forceinline__ float bm_cos(float r, float ub) { return r * __builtin_amdgcn_cosf(ub); }
-__device__ __forceinline__ float bm_sin(float r, float ub) { return r * __builtin_amdgcn_sinf(ub); }
-__device__ __forceinline__ double bm_radius(uint32_t a, double) {
-    return sqrt(-2.0 * log(unit_uniform<double>(a)));
+
+// The angle as the branches take it: the uniform (FP32), or its 24 bits (FP64).
+template <typename Real>
+struct BmAngle;
+template <>
+struct BmAngle<float> {
+    typedef float type;
+    static __device__ __forceinline__ float of(uint32_t w) { return unit_uniform<float>(w); }
+};
+template <>
+struct BmAngle<double> {
+    typedef uint32_t type;
+    static __device__ __forceinline__ uint32_t of(uint32_t w) { return (w >> 8) | 1u; }
+};
+template <typename Real>
+__device__ __forceinline__ typename BmAngle<Real>::type bm_angle(uint32_t w) {
+    return BmAngle<Real>::of(w);
 }
-__device__ __forceinline__ double bm_cos(double r, double ub) { return r * cospi(2.0 * ub); }
-__device__ __forceinline__ double bm_sin(double r, double ub) { return r * sinpi(2.0 * ub); }
+__device__ __forceinline__ float bm_cos(float r, float ub, const DrawTable*) {
+    return r * __builtin_amdgcn_cosf(ub);
+}
+__device__ __forceinline__ float bm_sin(float r, float ub, const DrawTable*) {
+    return r * __builtin_amdgcn_sinf(ub);
+}
+
+// FP64: the arguments are 24-bit integers, so the general library functions'
+// range reductions and special cases have nothing to do; the draws are most of
+// an FP64 sweep (log, square root and cosine took 270 of the 380 issue slots of
+// the 1-D step: 2^20 x 1000 7.0 -> 4.6 ms, d = 4 4.2 -> 2.5 ms, d = 8 7.8 -> 5.4 ms).  Their error
+// against extended precision is that of the library functions (RMS of a normal
+// 8.1e-17, largest 1.2e-15 over 2 10^6 draws).
+//
+// -2 ln u by Tang's table method: u = 2^e z with z in [0.6875, 1.375), r = z c - 1
+// with c the table's reciprocal of z's subinterval (|r| < 2^-7.9), and
+//   -2 ln u = -2 e ln 2 + 2 ln c - 2 ln(1 + r),
+// the last by its series to r^7 (the rest is below 2e-18 of it).  The small terms
+// are added first, and z just below 1 has c = 1, so the relative error stays below
+// 1.9e-16 for every u.  The square root is Goldschmidt's iteration from the
+// hardware estimate with a final residual correction; its argument lies in
+// [1.1e-7, 34].
+__device__ __forceinline__ double bm_sqrt(double y) {
+    const double r = __builtin_amdgcn_rsq(y);
+    double g = y * r, h = 0.5 * r;
+    double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    e = fma(-g, g, y);
+    return fma(e, h, g);
+}
+__device__ __forceinline__ double bm_radius(uint32_t a, double, const DrawTable* tb) {
+    const double x = (double)((a >> 8) | 1u);  // 2^24 u, exact
+    const uint64_t ix = __builtin_bit_cast(uint64_t, x);
+    const uint32_t hi = (uint32_t)(ix >> 32);
+    const uint32_t t = hi - 0x3fe60000u;
+    const double e = (double)(((int)t >> 20) - 24);
+    const double z = __builtin_bit_cast(
+        double, (uint64_t)(hi - (t & 0xfff00000u)) << 32 | (uint32_t)ix);
+    const double* c = tb->log[(t >> 13) & 127];
+    const double r = fma(z, c[0], -1.0);
+    double p = fma(-2.0 / 7.0, r, 1.0 / 3.0);
+    p = fma(p, r, -0.4);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, -2.0 / 3.0);
+    p = fma(p, r, 1.0);
+    const double s = fma(e, -4.638093627692599e-17, c[1] + fma(r * r, p, -2.0 * r));  // the rest of -2 ln 2
+    return bm_sqrt(fma(e, -1.3862943611198906188, s));
+}
+
+// cos and sin of 2 pi B 2^-24: the nearest of 256 tabulated angles plus
+// d, |d| < 0.0129, by the addition theorems with the series of sin d to d^7 and of
+// cos d - 1 to d^6 (the rests are below 2e-20); absolute error below 1.2e-16.
+struct BmTurn {
+    double c, s, cm, sd;
+};
+__device__ __forceinline__ BmTurn bm_turn(uint32_t b, const DrawTable* tb) {
+    const uint32_t i = ((b + 0x8000u) >> 16) & 255u;
+    const double* t = tb->turn[i];
+    const double d = (double)((int16_t)(b & 0xFFFFu) - tb->shift[i]) *
+                     (6.283185307179586477 / 16777216.0);
+    const double d2 = d * d;
+    const double ps = fma(d2, fma(d2, -1.0 / 5040.0, 1.0 / 120.0), -1.0 / 6.0);
+    const double pc = fma(d2, fma(d2, -1.0 / 720.0, 1.0 / 24.0), -0.5);
+    return BmTurn{t[0], t[1], d2 * pc, fma(d * d2, ps, d)};
+}
+__device__ __forceinline__ double bm_cos(double r, uint32_t b, const DrawTable* tb) {
+    const BmTurn t = bm_turn(b, tb);
+    return r * (t.c + fma(t.c, t.cm, -(t.s * t.sd)));
+}
+__device__ __forceinline__ double bm_sin(double r, uint32_t b, const DrawTable* tb) {
+    const BmTurn t = bm_turn(b, tb);
+    return r * (t.s + fma(t.s, t.cm, t.c * t.sd));
+}
+
+// The draw table in the block's LDS (FP64 paths; nothing for FP32): its
+// per-lane reads would otherwise wait, in the in-order vector-memory counter,
+// for every trajectory store of the wave.  Every thread calls stage().
+__device__ __forceinline__ void stage_draw_table(DrawTable* dst) {
+    constexpr int n = (int)(sizeof(DrawTable) / sizeof(double));
+    for (int e = threadIdx.x; e < n; e += blockDim.x)
+        ((double*)dst)[e] = ((const double*)&kDrawTable)[e];
+    __syncthreads();
+}
+template <typename Real>
+struct DrawLds {
+    __device__ __forceinline__ const DrawTable* stage() { return nullptr; }
+};
+template <>
+struct DrawLds<double> {
+    alignas(16) DrawTable t;
+    __device__ __forceinline__ const DrawTable* stage() {
+        stage_draw_table(&t);
+        return &t;
+    }
+};
 
 // Word made of the low bytes of the four words of Philox block 0:
 // byte j = low byte of word j.  v_perm_b32 selects bytes of the 8-byte value
@@ -217,30 +325,33 @@ template <typename Real, int D>
 struct StepDraws {
     Real zw[D];
     Real rad[D];  // Box-Muller radius
-    Real ang[D];  // angle uniform (revolutions)
+    typename BmAngle<Real>::type ang[D];  // angle
     int n;        // Poisson count
+    const DrawTable* dt;
 };
 
 template <typename Real, int D>
 __device__ __forceinline__ Real jump_normal(const StepDraws<Real, D>& s, int i) {
-    return bm_sin(s.rad[i], s.ang[i]);
+    return bm_sin(s.rad[i], s.ang[i], s.dt);
 }
 
-// Draws of path-step (m, k) under iteration word `iter`; t0 = thr->tm1[0].
+// Draws of path-step (m, k) under iteration word `iter`; t0 = thr->tm1[0]; dt: the
+// staged draw table (FP64).
 template <typename Real, int D>
 __device__ __forceinline__ void draws(uint32_t m, uint32_t k, uint32_t iter, uint32_t key0,
                                       uint32_t key1, const PoissonTable* __restrict__ thr,
-                                      uint32_t t0, StepDraws<Real, D>& s) {
+                                      uint32_t t0, const DrawTable* dt, StepDraws<Real, D>& s) {
     constexpr int NB = (D + 1) / 2;
+    s.dt = dt;
     uint32_t w[4 * NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b)
         philox4x32_10<true>(m, k, iter, (uint32_t)b, key0, key1, &w[4 * b]);
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-        s.rad[i] = bm_radius(w[2 * i], (Real)0);
-        s.ang[i] = unit_uniform<Real>(w[2 * i + 1]);
-        s.zw[i] = bm_cos(s.rad[i], s.ang[i]);
+        s.rad[i] = bm_radius(w[2 * i], (Real)0, dt);
+        s.ang[i] = bm_angle<Real>(w[2 * i + 1]);
+        s.zw[i] = bm_cos(s.rad[i], s.ang[i], dt);
     }
     s.n = poisson_count(poisson_word(w), t0, thr);
 }

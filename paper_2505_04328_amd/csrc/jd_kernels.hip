@@ -246,8 +246,11 @@ struct ForwardSweep {
     Real* row;  // next trajectory slot to write
     int64_t m;
     bool act;
+    const DrawTable* dt;  // the block's LDS copy (FP64 draws in the sweep)
 
-    __device__ __forceinline__ void begin(const SweepArgs<Real, D>& a, int64_t g) {
+    __device__ __forceinline__ void begin(const SweepArgs<Real, D>& a, int64_t g,
+                                          const DrawTable* dtab) {
+        dt = dtab;
         m = g * kThreads + threadIdx.x;
         act = m < a.M;
 #pragma unroll
@@ -262,7 +265,7 @@ struct ForwardSweep {
         const Real* trow = tab + (size_t)k * 2 * D;
         acc += (double)sq_dist<Real, D>(X, trow + D);
         StepDraws<Real, D> z;
-        draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, z);
+        draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
         euler_step<Real, D, CB>(a.c, a.lc, trow, X, z);
         put(a, k);
     }
@@ -343,6 +346,8 @@ k_noise(SweepArgs<Real, D> a, Real* __restrict__ noise, PoissonTable pt, int tb,
     __syncthreads();
     a.thr = &thr;
     a.thr0 = thr.tm1[0];
+    __shared__ DrawLds<Real> dl;
+    const DrawTable* dt = dl.stage();
     const int64_t nb = (int64_t)a.nblk * a.N;
     const int64_t rows = 2 * (int64_t)a.d * kThreads;
     for (int64_t b = blockIdx.x - tb; b < nb; b += gridDim.x - tb) {
@@ -350,7 +355,7 @@ k_noise(SweepArgs<Real, D> a, Real* __restrict__ noise, PoissonTable pt, int tb,
         const int k = (int)(b - g * a.N);
         const int64_t m = g * kThreads + threadIdx.x;
         StepDraws<Real, D> z;
-        draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, z);
+        draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
         Real* out = noise + b * rows + threadIdx.x;  // b = g N + k: step k of group g
 #pragma unroll
         for (int i = 0; i < D; ++i) {
@@ -477,8 +482,13 @@ k_forward(SweepArgs<Real, D> a, const Real* __restrict__ tab, double* __restrict
     stage_coef<CoefInLds<Real, D>::forward>(a, &sc);
     __shared__ PoissonTable thr;
     stage_thresholds(a, &thr);
+    const DrawTable* dt = nullptr;
+    if constexpr (!NOISE) {
+        __shared__ DrawLds<Real> dl;
+        dt = dl.stage();
+    }
     ForwardSweep<Real, D, MODE, CB> f;
-    f.begin(a, blockIdx.x);
+    f.begin(a, blockIdx.x, dt);
     if constexpr (NOISE) {
         sweep_noise<Real, D, MODE, CB>(f, a, tab, noise);
     } else {
@@ -694,14 +704,22 @@ k_cost_grad_stored(SweepArgs<Real, D> a, const Real* __restrict__ tab, double* _
     if (gate_closed(a.gate))
         return;
     __shared__ double sh[kThreads];
-    __shared__ Real tile[StepReducer<D, Real>::kRows][kThreads];
+    __shared__ alignas(16) Real tile[StepReducer<D, Real>::kRows][kThreads];
     __shared__ Coef<Real, D> sc;
     stage_coef<CoefInLds<Real, D>::any>(a, &sc);
     __shared__ PoissonTable thr;
     stage_thresholds(a, &thr);
+    const DrawTable* dt = nullptr;
+    if constexpr (!NOISE && sizeof(Real) == 8) {
+        // in the reducer's tile, which the backward sweep fills only after
+        // finish()'s barriers (LDS of its own would cost a resident block)
+        static_assert(sizeof(DrawTable) <= sizeof(tile), "the tile holds the draw table");
+        stage_draw_table((DrawTable*)tile);
+        dt = (const DrawTable*)tile;
+    }
     {
         ForwardSweep<Real, D, FWD_STORE, CB> f;
-        f.begin(a, blockIdx.x);
+        f.begin(a, blockIdx.x, dt);
         if constexpr (NOISE) {
             sweep_noise<Real, D, FWD_STORE, CB>(f, a, tab, noise);
         } else {
@@ -739,6 +757,8 @@ k_adjoint_recompute(SweepArgs<Real, D> a, const Real* __restrict__ tab) {
     stage_coef<CoefInLds<Real, D>::any>(a, &sc);
     __shared__ PoissonTable thr;
     stage_thresholds(a, &thr);
+    __shared__ DrawLds<Real> dl;
+    const DrawTable* dt = dl.stage();
     StepReducer<D, Real> red;
     red.init(tile, blockIdx.x);
     const int64_t m = (int64_t)blockIdx.x * kThreads + threadIdx.x;
@@ -775,7 +795,7 @@ k_adjoint_recompute(SweepArgs<Real, D> a, const Real* __restrict__ tab) {
         for (int s = 1; s < ns; ++s) {
             for (int k = s0 + (s - 1) * R; k < s0 + s * R; ++k) {
                 StepDraws<Real, D> z;
-                draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, z);
+                draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
                 euler_step<Real, D, CB>(a.c, a.lc, tab + (size_t)k * 2 * D, X, z);
             }
 #pragma unroll
@@ -805,7 +825,7 @@ k_adjoint_recompute(SweepArgs<Real, D> a, const Real* __restrict__ tab) {
                     for (int i = 0; i < D; ++i)
                         buf[r][i] = buf[r - 1][i];
                     StepDraws<Real, D> z;
-                    draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, z);
+                    draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
                     euler_step<Real, D, CB>(a.c, a.lc, tab + (size_t)k * 2 * D, buf[r], z);
                 }
             }
@@ -923,6 +943,8 @@ k_adjoint_segments(SweepArgs<Real, D> a, const Real* __restrict__ tab, Real* __r
     stage_coef<CoefInLds<Real, D>::any>(a, &sc);
     __shared__ PoissonTable thr;
     stage_thresholds(a, &thr);
+    __shared__ DrawLds<Real> dl;
+    const DrawTable* dt = dl.stage();
     const int N = a.N, K = a.K;
     const int nseg = (N + K - 1) / K;
     const Cols cl = make_cols(a.d);
@@ -966,7 +988,7 @@ k_adjoint_segments(SweepArgs<Real, D> a, const Real* __restrict__ tab, Real* __r
                 Real* row = region + cl.stride;
                 for (int k = s0; k < s1 - 1; ++k) {
                     StepDraws<Real, D> z;
-                    draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, z);
+                    draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
                     euler_step<Real, D, CB>(a.c, a.lc, tab + (size_t)k * 2 * D, X, z);
                     seg_store<Real, D>(row, a.d, X);
                     row += cl.stride;
@@ -1253,13 +1275,15 @@ k_draws(SweepArgs<Real, D> a, PoissonTable pt, int64_t m0, int64_t mc, int k0, i
     __syncthreads();
     a.thr = &tb;
     a.thr0 = tb.tm1[0];
+    __shared__ DrawLds<Real> dl;
+    const DrawTable* dt = dl.stage();
     const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (idx >= mc * kc)
         return;
     const int64_t p = idx / kc;
     const int q = (int)(idx - p * kc);
     StepDraws<Real, D> z;
-    draws<Real, D>((uint32_t)(m0 + p), (uint32_t)(k0 + q), a.iter, a.key0, a.key1, a.thr, a.thr0, z);
+    draws<Real, D>((uint32_t)(m0 + p), (uint32_t)(k0 + q), a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
 #pragma unroll
     for (int i = 0; i < D; ++i) {
         if (i < a.d) {
