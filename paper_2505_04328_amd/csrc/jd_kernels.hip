@@ -330,7 +330,7 @@ template <typename Real, int D>
 __global__ void __launch_bounds__(kThreads)
 k_noise(SweepArgs<Real, D> a, Real* __restrict__ noise, PoissonTable pt, int tb,
         const double* __restrict__ u, const double* __restrict__ xd, Real* __restrict__ tab,
-        BMat B, WsHeader* hdr, int clear_flag) {
+        BMat B, WsHeader* hdr, int clear_flag, int ks) {
     if (gate_closed(a.gate))
         return;
     if ((int)blockIdx.x < tb) {
@@ -348,21 +348,26 @@ k_noise(SweepArgs<Real, D> a, Real* __restrict__ noise, PoissonTable pt, int tb,
     a.thr0 = thr.tm1[0];
     __shared__ DrawLds<Real> dl;
     const DrawTable* dt = dl.stage();
-    const int64_t nb = (int64_t)a.nblk * a.N;
+    // the block's group and run of steps
+    const int per = (a.N + ks - 1) / ks;  // runs per group
     const int64_t rows = 2 * (int64_t)a.d * kThreads;
-    for (int64_t b = blockIdx.x - tb; b < nb; b += gridDim.x - tb) {
-        const int64_t g = b / a.N;
-        const int k = (int)(b - g * a.N);
+    for (int64_t b = blockIdx.x - tb; b < (int64_t)a.nblk * per; b += gridDim.x - tb) {
+        const int64_t g = b / per;
+        const int k0 = (int)(b - g * per) * ks;
+        const int k1 = k0 + ks < a.N ? k0 + ks : a.N;
         const int64_t m = g * kThreads + threadIdx.x;
-        StepDraws<Real, D> z;
-        draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
-        Real* out = noise + b * rows + threadIdx.x;  // b = g N + k: step k of group g
+        Real* out = noise + (g * a.N + k0) * rows + threadIdx.x;
+#pragma unroll 2
+        for (int k = k0; k < k1; ++k, out += rows) {
+            StepDraws<Real, D> z;
+            draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
 #pragma unroll
-        for (int i = 0; i < D; ++i) {
-            if (i < a.d) {
-                out[i * kThreads] = z.zw[i];
-                out[(a.d + i) * kThreads] =
-                    z.n != 0 ? jump_increment<Real, D>(a.c, z, i) : (Real)-0.0;
+            for (int i = 0; i < D; ++i) {
+                if (i < a.d) {
+                    out[i * kThreads] = z.zw[i];
+                    out[(a.d + i) * kThreads] =
+                        z.n != 0 ? jump_increment<Real, D>(a.c, z, i) : (Real)-0.0;
+                }
             }
         }
     }
@@ -1456,11 +1461,22 @@ hipError_t launch_forward(const HostProblem& p, const HostRun& r, const void* ta
     return hipGetLastError();
 }
 
+// Steps per block of the noise launch: a block's start (its arguments, the draw
+// table, the thresholds) takes as long as a step or two, so it runs several where
+// enough blocks remain to fill the chip (1024 runs).  One forward call with the
+// table, FP64: 10^4 paths x 100 34.3 us at 1 step, 31.4 at 3; 65536 x 300 211 at 1, 146
+// at 8, 145 at 16; FP32 d = 4, 16000 x 300: 104 at 1, 95 at 8.
+static int noise_run(const HostRun& r, int N) {
+    const int64_t n = (int64_t)r.nblk * N / 1024;
+    return n < 1 ? 1 : n > 8 ? 8 : (int)n;
+}
+
 hipError_t launch_setup_noise(const HostProblem& p, const HostRun& r, const double* u, void* tab,
                               void* noise, WsHeader* hdr, int clear_flag, hipStream_t st,
                               Gate gate) {
     const int64_t tb = table_blocks(p.N, p.D);
-    const int64_t nb = (int64_t)r.nblk * p.N;
+    const int ks = noise_run(r, p.N);
+    const int64_t nb = (int64_t)r.nblk * ((p.N + ks - 1) / ks);
     const unsigned grid = (unsigned)(tb + (nb < kNoiseGrid ? nb : kNoiseGrid));
     const BMat B = make_B(p);
 #define JD_NOISE(T, DD)                                                                           \
@@ -1468,7 +1484,7 @@ hipError_t launch_setup_noise(const HostProblem& p, const HostRun& r, const doub
         SweepArgs<T, DD> a = make_args<T, DD>(p, r);                                              \
         a.gate = gate;                                                                            \
         hipLaunchKernelGGL((k_noise<T, DD>), dim3(grid), dim3(kThreads), 0, st, a, (T*)noise,     \
-                           p.poisson, (int)tb, u, p.xd, (T*)tab, B, hdr, clear_flag);             \
+                           p.poisson, (int)tb, u, p.xd, (T*)tab, B, hdr, clear_flag, ks);             \
     } while (0)
     JD_DISPATCH(r.prec, p.D, JD_NOISE);
 #undef JD_NOISE

@@ -146,7 +146,7 @@ hipError_t launch_forward(const HostProblem& p, const HostRun& r, const void* ta
                           Gate gate = kNoGate, const void* noise = nullptr);
 // launch_setup and the noise table of iteration r.iter (noise_bytes(): the
 // Brownian normals and jump increments of every path-step) in one launch: the
-// table's blocks, then min(nblk N, kNoiseGrid) blocks of draws.
+// table's blocks, then a block of draws per run of steps of a group, at most kNoiseGrid.
 constexpr int64_t kNoiseGrid = 65536;
 hipError_t launch_setup_noise(const HostProblem& p, const HostRun& r, const double* u, void* tab,
                               void* noise, WsHeader* hdr, int clear_flag, hipStream_t st,
