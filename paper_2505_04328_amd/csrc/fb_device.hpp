@@ -970,15 +970,33 @@ struct FbJumps {
 };
 
 template <typename Real>
-__device__ __forceinline__ FbJumps<Real> fb_jumps(void* traj, int N, int64_t nblk) {
+__device__ __forceinline__ FbJumps<Real> fb_jumps_of(void* traj, int N, int64_t nblk, int64_t b,
+                                                     int lane) {
     FbJumps<Real> j;
     Real* base = (Real*)traj + (size_t)nblk * (N + 1) * 2 * kThreads;
-    j.st = base + (size_t)blockIdx.x * kFbJumpCap * kFbJumpComp * kThreads + threadIdx.x;
+    j.st = base + (size_t)b * kFbJumpCap * kFbJumpComp * kThreads + lane;
     int32_t* counts = (int32_t*)(base + (size_t)nblk * kFbJumpCap * kFbJumpComp * kThreads);
-    j.count = counts + (size_t)blockIdx.x * kThreads + threadIdx.x;
-    j.per = (uint8_t*)(counts + (size_t)nblk * kThreads) + (size_t)blockIdx.x * N * kThreads +
-            threadIdx.x;
+    j.count = counts + (size_t)b * kThreads + lane;
+    j.per = (uint8_t*)(counts + (size_t)nblk * kThreads) + (size_t)b * N * kThreads + lane;
     return j;
+}
+template <typename Real>
+__device__ __forceinline__ FbJumps<Real> fb_jumps(void* traj, int N, int64_t nblk) {
+    return fb_jumps_of<Real>(traj, N, nblk, blockIdx.x, (int)threadIdx.x);
+}
+
+// The draws of the jump that ends sub-step r of interval k: its normal S and
+// the normals of sub-step r + 1 (block r + 1).
+template <typename Real>
+__device__ __forceinline__ void fb_jump_draws(const FbArgs<Real>& a, uint32_t m, int k, int r,
+                                              Real& S, Real& zx, Real& zv) {
+    uint32_t w[4];
+    philox4x32_10<false>(m, (uint32_t)k, a.iter, (uint32_t)(r + 1), a.key0, a.key1, w);
+    S = bm_cos(bm_radius(w[2], (Real)0, a.dtab), bm_angle<Real>(w[3]), a.dtab);
+    const Real R = bm_radius(w[0], (Real)0, a.dtab);
+    const auto ub = bm_angle<Real>(w[1]);
+    zx = bm_cos(R, ub, a.dtab);
+    zv = bm_sin(R, ub, a.dtab);
 }
 
 // Sub-steps r0 .. r1 - 1 (at most up to n) of interval k of one particle,

@@ -1217,8 +1217,12 @@ template <typename Real>
 static hipError_t fb_adjoint_t(const FbHost& p, const HostRun& r, const void* tab, const void* traj,
                                double* apart, const WsHeader* hdr, bool surr, hipStream_t st,
                                Gate gate) {
-    if (!surr && fb_small_adjoint_ok(p, r))
-        return fb_small_adjoint<Real>(p, r, tab, traj, apart, st, gate);
+    const bool small = !surr && fb_small_adjoint_ok(p, r);
+    if (small) {
+        const hipError_t e = fb_small_adjoint<Real>(p, r, tab, traj, apart, st, gate);
+        if (e != hipSuccess || p.grid == 0)
+            return e;  // on the jump-adapted grid the blocks past the jump stack follow
+    }
     const FbTable t = fb_table_layout(p);
     FbArgs<Real> a = fb_args<Real>(p, r);
     a.thr = &hdr->poisson;
@@ -1234,12 +1238,12 @@ static hipError_t fb_adjoint_t(const FbHost& p, const HostRun& r, const void* ta
 #define FB_ADJ(NVP)                                                                               \
     do {                                                                                          \
         if (p.grid == 1) {                                                                        \
-            const bool rows = p.rate * p.dt <= fb_row_jumps<Real>();                                       \
+            const bool rows = !small && p.rate * p.dt <= fb_row_jumps<Real>();                    \
             if (rows)                                                                             \
                 hipLaunchKernelGGL((k_fb_adjoint_adapted_rows<Real, NVP>), dim3(nb),              \
                                    dim3(kThreads), 0, st, a, tb + t.mu, tb + t.zd, traj, apart);  \
             hipLaunchKernelGGL((k_fb_adjoint_adapted<Real, NVP>), dim3(nb), dim3(kThreads), 0,    \
-                               st, a, tb + t.mu, tb + t.zd, traj, apart, rows);                   \
+                               st, a, tb + t.mu, tb + t.zd, traj, apart, rows || small);          \
         } else if (p.np > 1) {                                                                    \
             if (G == 8) {                                                                         \
                 constexpr int RT = fb_ring_adj_threads<Real, NVP>();                              \

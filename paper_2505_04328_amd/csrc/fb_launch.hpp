@@ -50,14 +50,14 @@ size_t fb_svar_count(const FbHost& p);
 // Small particle counts (fb_small.hip).  Whether a forward / an adjoint sweep
 // takes those kernels, their workspace scratch (byte offsets; total 0 when
 // they are not taken) and the forward's split over workgroups.
-constexpr int kFbSmallCoef = 6;      // coefficients of an adjoint step
+constexpr int kFbSmallCoef = 6;      // values kept of an adjoint (sub-)step
 constexpr int kFbRowSlots = 16;      // particles per workgroup, independent particles
 constexpr int kFbRingRowSlots = 32;  // particles (with halos) per workgroup, rings
 inline int fb_row_slots(const FbHost& p) { return p.np == 1 ? kFbRowSlots : kFbRingRowSlots; }
 bool fb_small_forward_ok(const FbHost& p, const HostRun& r);
 bool fb_small_adjoint_ok(const FbHost& p, const HostRun& r);
 struct FbSmall {
-    size_t state, acc, coef, wgt, total;
+    size_t state, acc, start, coef, wgt, total;
 };
 FbSmall fb_small_layout(const FbHost& p, const HostRun& r);
 struct FbRowPlan {

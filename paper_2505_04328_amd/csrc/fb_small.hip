@@ -16,6 +16,7 @@
 //  k_fb_recur_ring    multiply-adds per step); writes the gradient weights
 //  k_fb_contract      the gradient's sum over particles of all steps at once,
 //                     with the matrix-core chains of k_fb_adjoint
+//  *_adapted          the same on the jump-adapted grid, per sub-step
 //
 // Every state, adjoint and weight is computed by the same operations in the
 // same order as in k_fb_forward and k_fb_adjoint, and the FP32 matrix-core
@@ -24,7 +25,8 @@
 //
 // Measured (MI355X): 2000 particles x 50 steps of the 10 x 10 grid, FP32:
 // forward 127 -> 30 us, adjoint 109 -> 18 us (5.5 + 8.2 + 4.4); one FP64 ring of
-// 2000 x 50: 1055 -> 75 us (four launches) and 1015 -> 39 us (10 + 20 + 8.4).
+// 2000 x 50: 1055 -> 75 us (four launches) and 1015 -> 39 us (10 + 20 + 8.4).  Jump-adapted
+// grid, 2000 x 50: forward 214 -> 68 us, adjoint 364 -> 65 us (FP64 679 -> 93, 672 -> 86).
 #include "fb_device.hpp"
 
 namespace jd {
@@ -267,6 +269,172 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
             f.acc[p] = acc;
         return;
     }
+    const double C = act && j == 0 ? acc : 0.0;
+    if (a.dcost != nullptr && act && j == 0) {
+        const int64_t e = p - a.dm0;
+        if (e >= 0 && e < a.dcount)
+            a.dcost[e] = C;
+    }
+    const double s = block_sum<TPB>(C, sh);
+    if (threadIdx.x == 0)
+        cpart[blockIdx.x] = s;
+}
+
+// ---------------------------------------------------------------------------
+// Jump-adapted grid.
+
+// Draws of one interval: the sub-step-0 normals, the count, and for an interval
+// with jumps the first jump's offset and normal and the normals of the sub-step
+// after it (later jumps of the interval are drawn where they happen).
+template <typename Real>
+struct alignas(4 * sizeof(Real)) FbRowInterval {
+    Real zx, zv, n, a1, s1, zx1, zv1, pad;
+};
+
+// k_fb_forward_adapted for few particles: one particle per row of 16 lanes, which
+// takes its sub-steps one after another (the rows of a wave are in step only at
+// the batches of 16 intervals).  Bound by one sub-step's chain of dependent
+// operations (0.8 us): in k_fb_forward_adapted a wave of 64 particles runs the
+// largest count of sub-steps of any of them, each with its own long chain.
+template <typename Real, int W, bool STORE>
+__global__ void __launch_bounds__(16 * kFbRowSlots)
+k_fb_forward_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
+                          const Real* __restrict__ zd, void* traj, double* __restrict__ cpart,
+                          int nvp) {
+    if (gate_closed(a.gate))
+        return;
+    constexpr int TPB = 16 * kFbRowSlots;
+    constexpr int WS = fb_row_stride(W);
+    constexpr int NP = (16 * W * W + TPB - 1) / TPB;
+    __shared__ PoissonTable thr;
+    fb_stage_thresholds(a, &thr);
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
+    __shared__ alignas(16) Real mus[16][W][WS];
+    __shared__ FbRowInterval<Real> dr[kFbRowSlots][17];
+    __shared__ Real zds[17][2];
+    __shared__ double sh[TPB];
+    const int row = threadIdx.x >> 4, j = threadIdx.x & 15;
+    const int64_t p = (int64_t)blockIdx.x * kFbRowSlots + row;
+    const bool act = p < a.M;
+    const int64_t b = p / kThreads;  // every slot of the nblk blocks has a row
+    const int l = (int)(p % kThreads);
+    Real* const trow = STORE ? (Real*)traj + (size_t)b * (a.N + 1) * 2 * kThreads + l : nullptr;
+    FbJumps<Real> jumps{};
+    if (STORE)
+        jumps = fb_jumps_of<Real>(traj, a.N, a.nblk, b, l);
+    Real x, v, cx = 0, cv = 0;
+    double acc = 0.0;
+    auto put = [&](int k) {
+        if (STORE && j < 2)
+            trow[((size_t)k * 2 + j) * kThreads] = j == 0 ? x : v;
+        if (act && j == 0)
+            fb_dump(a, a.dX, k, p, x, v);
+    };
+    fb_initial(a, (uint32_t)p, x, v);
+    put(0);
+    Real pre[NP];
+    auto fetch = [&](int kb) {
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int e = q * TPB + (int)threadIdx.x;
+            const int s = e / (W * W), i = e / W % W, c = e % W;
+            const bool in = e < 16 * W * W && kb + s < a.N && i < a.nx && c < nvp;
+            pre[q] = in ? mu[((size_t)(kb + s) * a.nx + i) * nvp + c] : (Real)0;
+        }
+    };
+    fetch(0);
+    int nj = 0;
+    for (int kb = 0; kb < a.N; kb += 16) {
+        const int ke = a.N - kb < 16 ? a.N : kb + 16;
+        lds_barrier();  // the previous batch's readers are done
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            const int e = q * TPB + (int)threadIdx.x;
+            if (e < 16 * W * W)
+                mus[e / (W * W)][e / W % W][e % W] = pre[q];
+        }
+        if (threadIdx.x < 34 && kb + (int)threadIdx.x / 2 <= a.N)
+            zds[threadIdx.x / 2][threadIdx.x % 2] = zd[2 * kb + threadIdx.x];
+        if (kb + 16 < a.N)
+            fetch(kb + 16);
+        {
+            // lane j: the draws of interval kb + j
+            FbRowInterval<Real> d;
+            d.a1 = 1;
+            d.s1 = d.zx1 = d.zv1 = d.pad = 0;
+            uint32_t w[4];
+            philox4x32_10<false>((uint32_t)p, (uint32_t)(kb + j), a.iter, 0u, a.key0, a.key1, w);
+            const int n = poisson_count(poisson_word(w), a.thr0, a.thr);
+            const Real R = bm_radius(w[0], (Real)0, a.dtab);
+            const auto ub = bm_angle<Real>(w[1]);
+            d.zx = bm_cos(R, ub, a.dtab);
+            d.zv = bm_sin(R, ub, a.dtab);
+            d.n = (Real)n;
+            if (n > 0) {
+                d.a1 = fb_next_offset(a, (uint32_t)p, kb + j, 0, n, (Real)0);
+                fb_jump_draws(a, (uint32_t)p, kb + j, 0, d.s1, d.zx1, d.zv1);
+            }
+            dr[row][j] = d;
+            if (STORE && kb + j < a.N)
+                jumps.per[(size_t)(kb + j) * kThreads] = (uint8_t)n;
+        }
+        lds_barrier();
+        int k = kb, r = 0;
+        FbRowInterval<Real> d = dr[row][0];
+        Real a0 = 0, a1 = d.a1, zx = d.zx, zv = d.zv;
+        while (k < ke) {
+            const int n = (int)d.n;
+            const bool whole = n == 0;
+            const Real len = whole ? a.dt : (a1 - a0) * a.dt;
+            Real m[W];
+#pragma unroll
+            for (int c = 0; c < W; ++c)
+                m[c] = mus[k - kb][j < W ? j : 0][c];
+            const Real u = row_control<Real, W>(a, m, j, x, v);
+            acc += (double)((whole ? a.hadt : (Real)0.5 * a.alpha * len) * u * u);
+            fb_euler(a, len, whole ? a.sqb1 : a.b1 * sqrt(len), whole ? a.sqb2 : a.b2 * sqrt(len),
+                     u, zx, zv, x, v, cx, cv);
+            if (r < n) {
+                Real S = d.s1, zx1 = d.zx1, zv1 = d.zv1;
+                if (r > 0)
+                    fb_jump_draws(a, (uint32_t)p, k, r, S, zx1, zv1);
+                v = fma(S, a.sbeta, a.gamma * v);
+                cv = a.gamma * cv;
+                zx = zx1;
+                zv = zv1;
+                if (STORE && nj < kFbJumpCap && j < 3)
+                    jumps.st[(size_t)(kFbJumpComp * nj + j) * kThreads] = j == 0   ? x
+                                                                          : j == 1 ? v
+                                                                                   : a1;
+                ++nj;
+            }
+            {
+                const Real* z = zds[k - kb];
+                Real tg[2];
+                fb_target(z, a1, tg);
+                acc += (double)(len * track(a, x, v, tg));
+            }
+            a0 = a1;
+            a1 = r + 1 < n ? fb_next_offset(a, (uint32_t)p, k, r + 1, n, a1) : (Real)1;
+            if (r < n) {
+                ++r;
+            } else {
+                put(k + 1);
+                ++k;
+                r = 0;
+                if (k < ke) {
+                    d = dr[row][k - kb];
+                    a0 = 0;
+                    a1 = d.a1;
+                    zx = d.zx;
+                    zv = d.zv;
+                }
+            }
+        }
+    }
+    if (STORE && j == 0)
+        *jumps.count = nj;
     const double C = act && j == 0 ? acc : 0.0;
     if (a.dcost != nullptr && act && j == 0) {
         const int64_t e = p - a.dm0;
@@ -569,6 +737,232 @@ k_fb_contract(FbArgs<Real> a, const void* traj, const Real* __restrict__ wgt,
     fb_hist_flush<false>(sh, wave, hist, 0, 1, 1, a.nx, a.nv, apart);
 }
 
+// ---------------------------------------------------------------------------
+// The jump-adapted adjoint in the same three parts.  Sub-step r of interval k is
+// the particle's sub-step q = k + (jumps before interval k) + r of N + (jumps); its
+// values stand at q, so that the recursion is one loop over q whatever the jumps.
+// Blocks with a particle past the jump stack are left to k_fb_adjoint_adapted.
+
+// Jumps before each interval: start[(b N + k) 256 + l].
+template <typename Real>
+__global__ void __launch_bounds__(64)
+k_fb_jump_starts(FbArgs<Real> a, const void* traj, uint8_t* __restrict__ start) {
+    if (gate_closed(a.gate))
+        return;
+    const int64_t q = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const int64_t b = q / kThreads;
+    const int l = (int)(q % kThreads);
+    const FbJumps<Real> j = fb_jumps_of<Real>(const_cast<void*>(traj), a.N, a.nblk, b, l);
+    uint8_t* out = start + (size_t)b * a.N * kThreads + l;
+    constexpr int U = 16;
+    int n = 0;
+    for (int k0 = 0; k0 < a.N; k0 += U) {
+        int c[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            c[i] = j.per[(size_t)(k0 + i < a.N ? k0 + i : a.N - 1) * kThreads];
+#pragma unroll
+        for (int i = 0; i < U; ++i)
+            if (k0 + i < a.N) {
+                out[(size_t)(k0 + i) * kThreads] = (uint8_t)n;
+                n += c[i];
+            }
+    }
+}
+
+// Values of sub-step q: coef[((b Q + q) 6 + c) 256 + l], Q = N + kFbJumpCap:
+//   0 u  1 u_x  2 u_v  3 share d / dt of the interval, its sign bit set where a
+//   jump ends the sub-step  4, 5 dJt/dz at its end state
+template <typename Real, int NVP>
+__global__ void __launch_bounds__(kThreads)
+k_fb_coef_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
+                  const void* traj, const uint8_t* __restrict__ start, Real* __restrict__ coef) {
+    if (gate_closed(a.gate))
+        return;
+    const int N = a.N, b = blockIdx.x / N, k = blockIdx.x - b * N, l = threadIdx.x;
+    const FbJumps<Real> jumps = fb_jumps_of<Real>(const_cast<void*>(traj), N, a.nblk, b, l);
+    if (__syncthreads_or(*jumps.count > kFbJumpCap))
+        return;
+    const Real* row = fb_row<Real>(const_cast<void*>(traj), N, b) + (size_t)k * 2 * kThreads;
+    Real x = row[0], v = row[kThreads];
+    const Real xe = row[2 * kThreads], ve = row[3 * kThreads];
+    const int n = jumps.per[(size_t)k * kThreads];
+    const int jb = start[((size_t)b * N + k) * kThreads + l];
+    Real* c = coef + ((size_t)b * (N + kFbJumpCap) + k + jb) * kFbSmallCoef * kThreads + l;
+    const Real* mk = mu + (size_t)k * a.nx * NVP;
+    const Real* zk = zd + 2 * k;
+    Real a0 = 0;
+    for (int r = 0; __builtin_amdgcn_ballot_w64(r <= n); ++r) {
+        // this sub-step's end: the next jump's stack entry, or z_{k+1}
+        Real ex = xe, ev = ve, a1 = 1;
+        fb_stack_entry(jumps, jb + r, r < n, ex, ev, a1);
+        Real pv[NVP], dpv[NVP];
+#pragma unroll
+        for (int q = 0; q < NVP; ++q)
+            pv[q] = bump_dq(fma(-(Real)q, a.eps * a.dvc, a.eps * (v - a.vc0)), dpv[q]);
+        Real u = 0, ux = 0, uv = 0;
+#pragma unroll 2
+        for (int i = 0; i < a.nx; ++i) {
+            Real dbx;
+            const Real bx = bump_dq(fma(-(Real)i, a.eps * a.dxc, a.eps * (x - a.xc0)), dbx);
+            const Real* rw = mk + i * NVP;
+            Real t = 0, sv = 0;
+#pragma unroll
+            for (int q = 0; q < NVP; ++q) {
+                t = fma(rw[q], pv[q], t);
+                sv = fma(rw[q], dpv[q], sv);
+            }
+            u = fma(bx, t, u);
+            ux = fma(dbx, t, ux);
+            uv = fma(bx, sv, uv);
+        }
+        ux *= (Real)-2 * a.eps;  // d carries b'(r) / (-2 eps)
+        uv *= (Real)-2 * a.eps;
+        Real tg[2], gx, gv;
+        fb_target(zk, a1, tg);
+        track_grad(a, ex, ev, tg, gx, gv);
+        if (r <= n) {
+            c[0] = u;
+            c[kThreads] = ux;
+            c[2 * kThreads] = uv;
+            const Real share = n == 0 ? (Real)1 : a1 - a0;
+            c[3 * kThreads] = copysign(share, r < n ? (Real)-1 : (Real)1);
+            c[4 * kThreads] = gx;
+            c[5 * kThreads] = gv;
+            c += kFbSmallCoef * kThreads;
+        }
+        x = ex;
+        v = ev;
+        a0 = a1;
+    }
+}
+
+// The recursion, one particle per lane; a batch of sub-steps is loaded while the
+// one before is swept.  Weights: wgt[(b Q + q) 256 + l].
+template <typename Real>
+__global__ void __launch_bounds__(64)
+k_fb_recur_adapted(FbArgs<Real> a, const void* traj, const uint8_t* __restrict__ start,
+                   const Real* __restrict__ coef, Real* __restrict__ wgt) {
+    if (gate_closed(a.gate))
+        return;
+    constexpr int U = 8;
+    const int64_t slot = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const int64_t b = slot / kThreads;
+    const int l = (int)(slot % kThreads);
+    const bool act = slot < a.M;
+    const FbJumps<Real> jumps = fb_jumps_of<Real>(const_cast<void*>(traj), a.N, a.nblk, b, l);
+    const int Q = a.N + kFbJumpCap;
+    // a particle past its stack belongs to a block that the general kernel
+    // sweeps: its weights are not read
+    const int nq = *jumps.count > kFbJumpCap ? 0 : a.N + *jumps.count;
+    int last = nq;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1)
+        last = max(last, __shfl_xor(last, o));
+    last = __builtin_amdgcn_readfirstlane(last);
+    if (last == 0)
+        return;
+    const Real* cb = coef + (size_t)b * Q * kFbSmallCoef * kThreads + l;
+    Real* wb = wgt + (size_t)b * Q * kThreads + l;
+    const uint8_t* sb = start + (size_t)b * a.N * kThreads + l;
+    Real lx = 0, lv = 0;
+    int k = a.N - 1;  // the interval at hand (dumps)
+    Real ca[U][kFbSmallCoef], cc[U][kFbSmallCoef];
+    auto load = [&](int q, Real (&c)[U][kFbSmallCoef]) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            int qq = q - i < nq ? q - i : nq - 1;  // stay on what was written
+            qq = qq > 0 ? qq : 0;
+#pragma unroll
+            for (int e = 0; e < kFbSmallCoef; ++e)
+                c[i][e] = cb[((size_t)qq * kFbSmallCoef + e) * kThreads];
+        }
+    };
+    auto sweep = [&](int q0, const Real (&c)[U][kFbSmallCoef]) {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const int q = q0 - i;
+            if (q >= 0 && q < nq) {
+                const Real u = c[i][0], ux = c[i][1], uv = c[i][2];
+                const Real share = fabs(c[i][3]), d = share * a.dt;
+                lx = fma(d, c[i][4], lx);
+                lv = fma(d, c[i][5], lv);
+                if (a.dlam != nullptr && act) {
+                    // the last sub-step of an interval ends at the uniform point k + 1
+                    const int end = k + (k + 1 < a.N ? (int)sb[(size_t)(k + 1) * kThreads] : nq - a.N);
+                    if (q == end)
+                        fb_dump(a, a.dlam, k + 1, slot, lx, lv);
+                    if (q == k + (int)sb[(size_t)k * kThreads] && k > 0)
+                        --k;
+                }
+                const Real lxm = lx, lvm = signbit(c[i][3]) ? a.gamma * lv : lv;
+                const Real w = share * fma(a.alpha, u, lvm);
+                wb[(size_t)q * kThreads] = act ? w : (Real)0;
+                const Real au = a.alpha * u;
+                lx = fma(d, fma(au, ux, (ux - a.eta) * lvm), lxm);
+                lv = fma(d, fma(au, uv, fma(uv, lvm, lxm)), lvm);
+            }
+        }
+    };
+    int q = last - 1;
+    load(q, ca);
+    for (;;) {
+        if (q - U >= 0)
+            load(q - U, cc);
+        sweep(q, ca);
+        q -= U;
+        if (q < 0)
+            break;
+        if (q - U >= 0)
+            load(q - U, ca);
+        sweep(q, cc);
+        q -= U;
+        if (q < 0)
+            break;
+    }
+}
+
+// The gradient's sums of one block and interval, with k_fb_adjoint_adapted's
+// chain: the sub-steps from the wave's largest count down.
+template <typename Real, int NVP>
+__global__ void __launch_bounds__(kThreads)
+k_fb_contract_adapted(FbArgs<Real> a, const void* traj, const uint8_t* __restrict__ start,
+                      const Real* __restrict__ wgt, double* __restrict__ apart) {
+    if (gate_closed(a.gate))
+        return;
+    const int N = a.N, b = blockIdx.x / N, k = blockIdx.x - b * N, l = threadIdx.x;
+    const FbJumps<Real> jumps = fb_jumps_of<Real>(const_cast<void*>(traj), N, a.nblk, b, l);
+    if (__syncthreads_or(*jumps.count > kFbJumpCap))
+        return;
+    __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
+    auto wave = fb_wave(sh);
+    const Real* row = fb_row<Real>(const_cast<void*>(traj), N, b) + (size_t)k * 2 * kThreads;
+    const Real xk = row[0], vk = row[kThreads];
+    const bool act = (int64_t)b * kThreads + l < a.M;
+    const int n = jumps.per[(size_t)k * kThreads];
+    const int jb = start[((size_t)b * N + k) * kThreads + l];
+    const Real* wb = wgt + ((size_t)b * (N + kFbJumpCap) + k + jb) * kThreads + l;
+    int nmax = 0;
+    while (__builtin_amdgcn_ballot_w64(n > nmax))
+        ++nmax;
+    for (int r = nmax; r >= 0; --r) {
+        const bool mine = r <= n;
+        Real x = xk, v = vk, o;
+        fb_stack_entry(jumps, jb + r - 1, mine && r > 0, x, v, o);
+        const Real w = mine && act ? wb[(size_t)r * kThreads] : (Real)0;
+        Real pv[NVP];
+        shapes_v<Real, NVP>(a, v, pv);
+        for (int i = 0; i < a.nx; ++i)
+            wave.put_x(i, bump_q(fma(-(Real)i, a.eps * a.dxc, a.eps * (x - a.xc0))));
+        wave.template put_vw<Real, NVP>(pv, w);
+        wave.add_live(__builtin_amdgcn_ballot_w64(mine && act));
+    }
+    FbHist<Real, 1> hist;
+    hist.cnt = 0;
+    hist.push(wave.acc);
+    fb_hist_flush<false>(sh, wave, hist, 0, 1, 1, a.nx, a.nv, apart);
+}
+
 // ===========================================================================
 // Launchers.
 
@@ -593,6 +987,20 @@ hipError_t fb_small_forward(const FbHost& p, const HostRun& r, const void* tab, 
     const Real* tb = (const Real*)tab;
     const FbSmall sm = fb_small_layout(p, r);
     const FbRowPlan pl = fb_row_plan(p, r, fb_row_slots(p));
+    if (p.grid == 1) {
+#define FB_ROWS_A(W, S)                                                                           \
+    hipLaunchKernelGGL((k_fb_forward_adapted_rows<Real, W, S>), dim3((unsigned)pl.blocks),        \
+                       dim3(16 * kFbRowSlots), 0, st, a, tb + t.mu, tb + t.zd, traj, cpart, p.nvp)
+        if (p.nx <= 10 && p.nv <= 10) {
+            if (traj != nullptr) FB_ROWS_A(10, true);
+            else FB_ROWS_A(10, false);
+        } else {
+            if (traj != nullptr) FB_ROWS_A(16, true);
+            else FB_ROWS_A(16, false);
+        }
+#undef FB_ROWS_A
+        return hipGetLastError();
+    }
     FbRows<Real> f = fb_rows<Real>(p, pl);
     Real* state = (Real*)((char*)p.small + sm.state);
     f.acc = (double*)((char*)p.small + sm.acc);
@@ -637,6 +1045,24 @@ hipError_t fb_small_adjoint(const FbHost& p, const HostRun& r, const void* tab, 
     const unsigned nb = (unsigned)r.nblk;
     const unsigned cells = nb * (unsigned)p.N;
     const unsigned cols = (unsigned)fb_partial_blocks(p, r) * (unsigned)p.N;
+    if (p.grid == 1) {
+        uint8_t* start = (uint8_t*)p.small + sm.start;
+        hipLaunchKernelGGL(k_fb_jump_starts<Real>, dim3(nb * (kThreads / 64)), dim3(64), 0, st, a,
+                           traj, start);
+#define FB_COEF(NVP)                                                                              \
+    hipLaunchKernelGGL((k_fb_coef_adapted<Real, NVP>), dim3(cells), dim3(kThreads), 0, st, a,     \
+                       tb + t.mu, tb + t.zd, traj, start, coef)
+        FB_DISPATCH_NVP(p.nvp, FB_COEF);
+#undef FB_COEF
+        hipLaunchKernelGGL(k_fb_recur_adapted<Real>, dim3(nb * (kThreads / 64)), dim3(64), 0, st, a,
+                           traj, start, coef, wgt);
+#define FB_CON(NVP)                                                                               \
+    hipLaunchKernelGGL((k_fb_contract_adapted<Real, NVP>), dim3(cells), dim3(kThreads), 0, st, a, \
+                       traj, start, wgt, apart)
+        FB_DISPATCH_NVP(p.nvp, FB_CON);
+#undef FB_CON
+        return hipGetLastError();
+    }
 #define FB_COEF(NVP)                                                                              \
     hipLaunchKernelGGL((k_fb_coef<Real, NVP>), dim3(cells), dim3(kThreads), 0, st, a, tb + t.mu,  \
                        tb + t.zd, tb + t.ks, traj, coef)

@@ -82,34 +82,52 @@ int fb_ring_groups(int np) { return np <= kBlock ? 1 : 8; }
 // 189 / 136 at 65536; FP64 58 / 276, 228 / 257, 431 / 261.  Rings of 8..256, by
 // computed slots: FP32 130 / 147 at 32000, 234 / 147 at 71680; FP64 155 / 268 at
 // 8960, 296 / 270 at 32000.  Rings of 500 and 2000: FP32 298 / 334 at 96000, 329 /
-// 334 at 128000; FP64 827 / 1080 at 96000.
+// 334 at 128000; FP64 827 / 1080 at 96000.  Jump-adapted grid (0.18 jumps per
+// interval): FP32 68 / 205 at 2000, 159 / 199 at 28672, 198 / 199 at 32768 (at 0.93
+// per interval 235 / 232); FP64 93 / 488 at 2000, 380 / 488 at 32768, 478 / 488 at 40960.
 static int64_t fb_small_forward_max(const FbHost& p, const HostRun& r) {
     if (p.np > 1 && p.G > 1)
         return 98304;
+    if (p.grid == 1)
+        return r.prec == JD_FP64 ? 32768 : 28672;
     return p.np > 1 && r.prec == JD_FP64 ? 24576 : 32768;
 }
 // Adjoint, split / one kernel: FP32 33 / 162 us at 2000 particles, 72 / 163 at
 // 32768, 118 / 169 at 65536 (the whole gradient 260 / 267), 171 / 172 at 100000 (309 /
 // 287); FP64 139 / 230 at 32768, 201 / 233 at 48000, 265 / 236 at 64000.  Rings of
 // more than 256: FP32 363 / 454 at 200000, 447 / 458 at 256000; FP64 894 / 1080 at
-// 200000, 1107 / 1083 at 256000.
+// 200000, 1107 / 1083 at 256000.  Jump-adapted grid: FP32 65 / 364 at 2000, 240 / 368 at
+// 49152, 351 / 370 at 65536 (100 steps: 371 / 507 at 49152, 514 / 507 at 65536); FP64 86 / 515
+// at 2000, 355 / 515 at 32768, 421 / 515 at 36864 (300 steps 1786 / 1675).
+// Jump-adapted grid: a block with a particle past its jump stack (32 entries) is swept
+// by the general kernel as well, so the split is taken up to 16 expected jumps (past
+// the stack: 1 particle in 10^4).
+constexpr double kFbSmallJumps = 16.0;
 static int64_t fb_small_adjoint_max(const FbHost& p, const HostRun& r) {
     if (p.np > 1 && p.G > 1)
         return 200000;
+    if (p.grid == 1)
+        return p.rate * p.T > kFbSmallJumps ? 0 : r.prec == JD_FP64 ? 32768 : 49152;
     return r.prec == JD_FP64 ? 49152 : 65536;
 }
 // The coefficients of all particle-steps stay in the workspace.
 constexpr size_t kFbSmallMaxBytes = (size_t)1 << 30;
 
+// Values of one slot that the split adjoint keeps: per step its coefficients
+// and weight, on the jump-adapted grid per sub-step.
+static size_t fb_small_cells(const FbHost& p) {
+    return (size_t)p.N + (p.grid == 1 ? kFbJumpStates : 0);
+}
 bool fb_small_adjoint_ok(const FbHost& p, const HostRun& r) {
-    return p.grid == 0 && r.mode == JD_STORE && r.M <= fb_small_adjoint_max(p, r) &&
-           (size_t)r.ldm * (size_t)p.N * (kFbSmallCoef + 1) * real_size(r.prec) <= kFbSmallMaxBytes;
+    return r.mode == JD_STORE && r.M <= fb_small_adjoint_max(p, r) &&
+           (size_t)r.ldm * fb_small_cells(p) * (kFbSmallCoef + 1) * real_size(r.prec) <=
+               kFbSmallMaxBytes;
 }
 
 // The row forward leaves the empty slots of a ring workgroup unwritten, which
 // only the split adjoint masks.
 bool fb_small_forward_ok(const FbHost& p, const HostRun& r) {
-    if (p.grid != 0 || (p.np > 1 && !fb_small_adjoint_ok(p, r)))
+    if (p.np > 1 && !fb_small_adjoint_ok(p, r))
         return false;
     const int slots = fb_row_slots(p);
     return fb_row_plan(p, r, slots).blocks * slots <= fb_small_forward_max(p, r);
@@ -125,7 +143,9 @@ FbSmall fb_small_layout(const FbHost& p, const HostRun& r) {
     off += rings ? up((size_t)2 * 4 * r.M * real_size(r.prec)) : 0;
     s.acc = off;
     off += rings ? up((size_t)r.M * sizeof(double)) : 0;
-    const size_t cells = (size_t)r.ldm * p.N * real_size(r.prec);
+    s.start = off;
+    off += adj && p.grid == 1 ? up((size_t)r.ldm * p.N) : 0;
+    const size_t cells = (size_t)r.ldm * fb_small_cells(p) * real_size(r.prec);
     s.coef = off;
     off += adj ? up(cells * kFbSmallCoef) : 0;
     s.wgt = off;
