@@ -939,13 +939,14 @@ k_fb_adjoint_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
 // bytes of them per load); its thread (e, c) sums the partials b = c, c + 8,
 // ... of entry e in order, and a fixed LDS tree adds the 8 chunk sums (one
 // serial chain of 2048 loads per entry was latency-bound; 8 entries per
-// workgroup read 64-byte pieces: f4 step 13.92 against 13.77 ms).
-constexpr int kFbFinEntries = 32;
+// workgroup read 64-byte pieces: f4 step 13.92 against 13.77 ms).  Each workgroup
+// leaves the sum of its entries' squares in gsq for k_fb_finalize_cost.
+constexpr int kFbFinEntries = kFbGsqEntries;
 constexpr int kFbFinChunks = kThreads / kFbFinEntries;
 
 __global__ void __launch_bounds__(kThreads)
 k_fb_finalize_grad(const double* __restrict__ apart, int nblk, int64_t NL, int64_t M,
-                   double* __restrict__ g, WsHeader* hdr, Gate gate) {
+                   double* __restrict__ g, double* __restrict__ gsq, WsHeader* hdr, Gate gate) {
     if (gate_closed(gate))
         return;
     __shared__ double sh[kThreads];
@@ -963,37 +964,60 @@ k_fb_finalize_grad(const double* __restrict__ apart, int nblk, int64_t NL, int64
             sh[threadIdx.x] += sh[threadIdx.x + kFbFinEntries * w];
         __syncthreads();
     }
+    double g2 = 0.0;
     if (c == 0 && q < NL) {
         const double gq = sh[e] / (double)M;
         g[q] = gq;
+        g2 = gq * gq;
         if (!isfinite(gq))
             hdr->nonfinite = 1;
     }
+    if (threadIdx.x < 64) {
+        g2 = wave_sum(g2);
+        if (threadIdx.x == 0)
+            gsq[blockIdx.x] = g2;
+    }
 }
 
-// One block: J = (1/M) sum of the block costs and, with g, dt sum g^2.
-__global__ void __launch_bounds__(kThreads)
+// One block: J = (1/M) sum of the block costs and, with gsq, dt sum g^2.  Bound by
+// the latency of its loads: 1024 threads, the squares summed by the blocks of
+// k_fb_finalize_grad (summed here over all N L entries by 256 threads this took
+// 7.8 us at 50 steps of 100 entries and 56 at 500).
+constexpr int kFbCostThreads = 1024;
+
+__global__ void __launch_bounds__(kFbCostThreads)
 k_fb_finalize_cost(const double* __restrict__ cpart, int nblk, int64_t M, double dt,
-                   const double* __restrict__ g, int64_t NL, double* __restrict__ J_out,
+                   const double* __restrict__ gsq, int64_t ngsq, double* __restrict__ J_out,
                    WsHeader* hdr, int slot, Gate gate) {
     if (gate_closed(gate))
         return;
-    __shared__ double sh[kThreads];
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads)
+    constexpr int W = kFbCostThreads / 64;
+    __shared__ double sh[W][2];
+    double s = 0.0, gg = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += kFbCostThreads)
         s += cpart[b];
-    const double csum = block_sum(s, sh);
-    double gg = 0.0;
-    if (g != nullptr) {
-        for (int64_t q = threadIdx.x; q < NL; q += kThreads)
-            gg += g[q] * g[q];
-        gg = block_sum(gg, sh);
+    if (gsq != nullptr)
+        for (int64_t q = threadIdx.x; q < ngsq; q += kFbCostThreads)
+            gg += gsq[q];
+    s = wave_sum(s);
+    gg = wave_sum(gg);
+    if (threadIdx.x % 64 == 0) {
+        sh[threadIdx.x / 64][0] = s;
+        sh[threadIdx.x / 64][1] = gg;
     }
+    __syncthreads();
     if (threadIdx.x == 0) {
+        double csum = 0.0;
+        gg = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            csum += sh[w][0];
+            gg += sh[w][1];
+        }
         const double J = csum / (double)M;
         if (slot == 0) {
             hdr->J = J;
-            if (g != nullptr)
+            if (gsq != nullptr)
                 hdr->gnorm2 = dt * gg;
         } else {
             hdr->J_trial = J;
@@ -1336,16 +1360,17 @@ hipError_t fb_launch_finalize_grad(const FbHost& p, const HostRun& r, const doub
                                    double* g, WsHeader* hdr, hipStream_t st, Gate gate) {
     const int64_t NL = (int64_t)p.N * p.L;
     hipLaunchKernelGGL(k_fb_finalize_grad,
-                       dim3((unsigned)((NL + kFbFinEntries - 1) / kFbFinEntries)), dim3(kThreads), 0,
-                       st, apart, fb_partial_blocks(p, r), NL, r.M, g, hdr, gate);
+                       dim3((unsigned)fb_gsq_count(p)), dim3(kThreads), 0, st, apart,
+                       fb_partial_blocks(p, r), NL, r.M, g, p.gsq, hdr, gate);
     return hipGetLastError();
 }
 
 hipError_t fb_launch_finalize_cost(const FbHost& p, const HostRun& r, const double* cpart,
                                    int ncpart, const double* g, double* J_out, WsHeader* hdr,
                                    int slot, hipStream_t st, Gate gate) {
-    hipLaunchKernelGGL(k_fb_finalize_cost, dim3(1), dim3(kThreads), 0, st, cpart, ncpart, r.M,
-                       p.dt, g, (int64_t)p.N * p.L, J_out, hdr, slot, gate);
+    hipLaunchKernelGGL(k_fb_finalize_cost, dim3(1), dim3(kFbCostThreads), 0, st, cpart, ncpart,
+                       r.M, p.dt, g != nullptr ? p.gsq : nullptr, fb_gsq_count(p), J_out, hdr, slot,
+                       gate);
     return hipGetLastError();
 }
 

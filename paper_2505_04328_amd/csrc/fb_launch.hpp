@@ -32,7 +32,15 @@ struct FbHost {
     uint64_t thr[32];     // Poisson(rate dt) thresholds
     PoissonTable poisson;
     void* small;          // the workspace's scratch of the small-count kernels (FbSmall)
+    double* gsq;          // the workspace's sums of squares of the gradient (fb_gsq_count())
 };
+
+// The gradient reduction's workgroups take kFbGsqEntries entries each and leave
+// the sum of their squares for the cost reduction that follows.
+constexpr int kFbGsqEntries = 32;
+inline int64_t fb_gsq_count(const FbHost& p) {
+    return ((int64_t)p.N * p.L + kFbGsqEntries - 1) / kFbGsqEntries;
+}
 
 // Per-step table in the path precision: mu rows (N x nx x nvp, zero-padded),
 // targets ((N+1) x 2), the Keilson-Storer factors (32 x 2) and the surrogate
@@ -98,6 +106,8 @@ int fb_partial_blocks(const FbHost& p, const HostRun& r);
 int fb_forward_blocks(const FbHost& p, const HostRun& r);
 // 256-slot groups per workgroup of the ring kernels for rings of np particles.
 int fb_ring_groups(int np);
+// fb_launch_finalize_cost with g (the gradient that fb_launch_finalize_grad of the
+// same evaluation wrote) also reduces ||g||^2.
 hipError_t fb_launch_finalize_grad(const FbHost& p, const HostRun& r, const double* apart,
                                    double* g, WsHeader* hdr, hipStream_t st, Gate gate = kNoGate);
 hipError_t fb_launch_finalize_cost(const FbHost& p, const HostRun& r, const double* cpart,

@@ -494,6 +494,14 @@ __device__ __forceinline__ void lds_barrier() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Deterministic FP64 sum over the 64 lanes of a wave (fixed tree; every lane).
+__device__ __forceinline__ double wave_sum(double v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+        v += __shfl_xor(v, o);
+    return v;
+}
+
 // Deterministic FP64 sum over a block of NT threads (fixed tree).
 template <int NT = kThreads>
 __device__ __forceinline__ double block_sum(double v, double* sh) {

@@ -155,7 +155,7 @@ int fb_prepare(const jd_fb_problem* prob, const jd_run* run, FbHost& p, HostRun&
 }
 
 struct FbLayout {
-    size_t hdr, ring, tab, cpart, apart, gbuf, ut, mom, svar, small, total;
+    size_t hdr, ring, tab, cpart, apart, gbuf, gsq, ut, mom, svar, small, total;
 };
 
 FbLayout fb_layout(const FbHost& p, const HostRun& r) {
@@ -174,6 +174,8 @@ FbLayout fb_layout(const FbHost& p, const HostRun& r) {
     off += round_up((size_t)r.nblk * p.N * p.L * sizeof(double), kAlign);
     L.gbuf = off;
     off += round_up((size_t)p.N * p.L * sizeof(double), kAlign);
+    L.gsq = off;
+    off += round_up((size_t)fb_gsq_count(p) * sizeof(double), kAlign);
     L.ut = off;
     off += round_up((size_t)p.N * p.L * sizeof(double), kAlign);
     // surrogate gradient: the forward's per-step moment partials (fitted
@@ -227,6 +229,7 @@ int fb_bind(FbHost& p, const HostRun& r, void* ws, size_t ws_bytes, FbWs& w) {
     w.mom = (double*)(base + L.mom);
     w.svar = (double*)(base + L.svar);
     p.small = base + L.small;
+    p.gsq = (double*)(base + L.gsq);
     return JD_OK;
 }
 
