@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libjd.so")
 SOURCES = ["jd_kernels.hip", "fb_kernels.hip", "fb_small.hip", "jd_api.cpp", "jd_feedback.cpp", "jd_server.cpp",
            "jd_noalloc.cpp", "jd_shapes.cpp"]
-HEADERS = ["jd_device.hpp", "jd_draw_table.hpp", "fb_device.hpp", "jd_launch.hpp", "fb_launch.hpp", "jd_host.hpp"]
+HEADERS = ["jd_device.hpp", "jd_draw_table.hpp", "jd_linesearch.hpp", "fb_device.hpp",
+           "jd_launch.hpp", "fb_launch.hpp", "jd_host.hpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("JD_OFFLOAD_ARCH", "gfx950")

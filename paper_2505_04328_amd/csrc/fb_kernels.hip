@@ -29,30 +29,50 @@
 // cost of Section 6.4 (eq. interacting_model, eq. coupled_ellipse, eq.
 // phonon_functional_tracking).
 #include "fb_device.hpp"
+#include "jd_linesearch.hpp"
 
 namespace jd {
 
 // ---------------------------------------------------------------------------
+// tr.g != null: block row y makes the table of trial point mu - zeta[y] g, also
+// written to ut.
+struct FbTrialPoint {
+    const double* g;
+    double* ut;
+    size_t stride;  // elements of a table
+    double zeta[kLsTrials];
+};
+
 template <typename Real>
 __global__ void __launch_bounds__(kThreads)
 k_fb_table(const double* __restrict__ mu, const double* __restrict__ zd, Real* __restrict__ tab,
            int N, int nx, int nv, int nvp, size_t off_zd, size_t off_ks, FbKs ks, WsHeader* hdr,
-           int clear_flag, PoissonTable pt, Gate gate) {
+           int clear_flag, PoissonTable pt, Gate gate, FbTrialPoint tr) {
     if (gate_closed(gate))
         return;
+    tab += blockIdx.y * tr.stride;
     const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const int64_t nmu = (int64_t)N * nx * nvp;
     if (idx < nmu) {
         const int64_t k = idx / (nx * nvp);
         const int rem = (int)(idx - k * nx * nvp);
         const int i = rem / nvp, l = rem - i * nvp;
-        tab[idx] = l < nv ? (Real)mu[(k * nx + i) * nv + l] : (Real)0;
+        double m = 0.0;
+        if (l < nv) {
+            const int64_t e = (k * nx + i) * nv + l;
+            m = mu[e];
+            if (tr.g != nullptr) {
+                m = m - tr.zeta[blockIdx.y] * tr.g[e];
+                tr.ut[blockIdx.y * ((size_t)N * nx * nv) + e] = m;
+            }
+        }
+        tab[idx] = (Real)m;
     }
     if (idx < 2 * (int64_t)(N + 1))
         tab[off_zd + idx] = zd != nullptr ? (Real)zd[idx] : (Real)0;
     if (idx < 64)
         tab[off_ks + idx] = (Real)ks.v[idx];
-    if (idx == 0) {
+    if (idx == 0 && blockIdx.y == 0) {
         if (clear_flag)
             hdr->nonfinite = 0;
         hdr->poisson = pt;
@@ -982,39 +1002,57 @@ k_fb_finalize_grad(const double* __restrict__ apart, int nblk, int64_t NL, int64
 // One block: J = (1/M) sum of the block costs and, with gsq, dt sum g^2.  Bound by
 // the latency of its loads: 1024 threads, the squares summed by the blocks of
 // k_fb_finalize_grad (summed here over all N L entries by 256 threads this took
-// 7.8 us at 50 steps of 100 entries and 56 at 500).
+// 7.8 us at 50 steps of 100 entries and 56 at 500).  Then the line-search step:
+// with an Armijo step the costs of tail.trials trials, nblk each, and their tests
+// (a launch of its own took 4.7 us).
 constexpr int kFbCostThreads = 1024;
 
 __global__ void __launch_bounds__(kFbCostThreads)
 k_fb_finalize_cost(const double* __restrict__ cpart, int nblk, int64_t M, double dt,
                    const double* __restrict__ gsq, int64_t ngsq, double* __restrict__ J_out,
-                   WsHeader* hdr, int slot, Gate gate) {
+                   WsHeader* hdr, int slot, Gate gate, LsTail tail) {
     if (gate_closed(gate))
         return;
     constexpr int W = kFbCostThreads / 64;
-    __shared__ double sh[W][2];
-    double s = 0.0, gg = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kFbCostThreads)
-        s += cpart[b];
-    if (gsq != nullptr)
+    __shared__ double sh[kFbCostThreads];
+    __shared__ double Jt[kLsTrials];
+    const int nt = tail.mode == kLsTailArmijo ? tail.trials : 1;
+    // sh[w][0..3]: the trials' cost sums of wave w, sh[w][4]: its sum of squares
+    double gg = 0.0;
+    if (gsq != nullptr) {
         for (int64_t q = threadIdx.x; q < ngsq; q += kFbCostThreads)
             gg += gsq[q];
-    s = wave_sum(s);
-    gg = wave_sum(gg);
-    if (threadIdx.x % 64 == 0) {
-        sh[threadIdx.x / 64][0] = s;
-        sh[threadIdx.x / 64][1] = gg;
+        gg = wave_sum(gg);
+    }
+    for (int t = 0; t < nt; ++t) {
+        double s = 0.0;
+        for (int b = threadIdx.x; b < nblk; b += kFbCostThreads)
+            s += cpart[(size_t)t * nblk + b];
+        s = wave_sum(s);
+        if (threadIdx.x % 64 == 0)
+            sh[threadIdx.x / 64 * 5 + t] = s;
+    }
+    if (threadIdx.x % 64 == 0)
+        sh[threadIdx.x / 64 * 5 + 4] = gg;
+    __syncthreads();
+    if ((int)threadIdx.x < nt) {
+        double csum = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            csum += sh[w * 5 + threadIdx.x];
+        Jt[threadIdx.x] = csum / (double)M;
     }
     __syncthreads();
+    if (tail.mode == kLsTailArmijo) {
+        armijo_step<kFbCostThreads>(hdr, tail, Jt, sh);
+        return;
+    }
     if (threadIdx.x == 0) {
-        double csum = 0.0;
         gg = 0.0;
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            csum += sh[w][0];
-            gg += sh[w][1];
-        }
-        const double J = csum / (double)M;
+        for (int w = 0; w < W; ++w)
+            gg += sh[w * 5 + 4];
+        const double J = Jt[0];
         if (slot == 0) {
             hdr->J = J;
             if (gsq != nullptr)
@@ -1027,6 +1065,8 @@ k_fb_finalize_cost(const double* __restrict__ cpart, int nblk, int64_t M, double
         // a trial's cost (slot 1) may overflow: the Armijo test rejects it
         if (slot == 0 && (!isfinite(J) || !isfinite(gg)))
             hdr->nonfinite = 1;
+        if (tail.mode == kLsTailAfterGrad)
+            ls_after_grad_step(hdr, tail.n);
     }
 }
 
@@ -1171,14 +1211,23 @@ hipError_t fb_launch_table(const FbHost& p, const HostRun& r, const double* mu, 
         n = 2 * (int64_t)(p.N + 1);
     if (n < 64)
         n = 64;
+    FbTrialPoint tr{};
+    if (p.ls != nullptr && p.ls->mode == kLsTailArmijo) {
+        tr.g = p.ls_g;
+        tr.ut = p.ls_ut;
+        tr.stride = t.count;
+        for (int i = 0; i < fb_trials_of(p); ++i)
+            tr.zeta[i] = p.ls->zeta[i];
+    }
+    const dim3 grid(fb_blocks(n), (unsigned)fb_trials_of(p));
     if (r.prec == JD_FP64)
-        hipLaunchKernelGGL(k_fb_table<double>, dim3(fb_blocks(n)), dim3(kThreads), 0, st, mu, p.zd,
-                           (double*)tab, p.N, p.nx, p.nv, p.nvp, t.zd, t.ks, ks, hdr, clear_flag,
-                           p.poisson, gate);
+        hipLaunchKernelGGL(k_fb_table<double>, grid, dim3(kThreads), 0, st, mu, p.zd, (double*)tab,
+                           p.N, p.nx, p.nv, p.nvp, t.zd, t.ks, ks, hdr, clear_flag, p.poisson,
+                           gate, tr);
     else
-        hipLaunchKernelGGL(k_fb_table<float>, dim3(fb_blocks(n)), dim3(kThreads), 0, st, mu, p.zd,
-                           (float*)tab, p.N, p.nx, p.nv, p.nvp, t.zd, t.ks, ks, hdr, clear_flag,
-                           p.poisson, gate);
+        hipLaunchKernelGGL(k_fb_table<float>, grid, dim3(kThreads), 0, st, mu, p.zd, (float*)tab,
+                           p.N, p.nx, p.nv, p.nvp, t.zd, t.ks, ks, hdr, clear_flag, p.poisson,
+                           gate, tr);
     return hipGetLastError();
 }
 
@@ -1368,9 +1417,12 @@ hipError_t fb_launch_finalize_grad(const FbHost& p, const HostRun& r, const doub
 hipError_t fb_launch_finalize_cost(const FbHost& p, const HostRun& r, const double* cpart,
                                    int ncpart, const double* g, double* J_out, WsHeader* hdr,
                                    int slot, hipStream_t st, Gate gate) {
+    LsTail tail{};
+    if (p.ls != nullptr)
+        tail = *p.ls;
     hipLaunchKernelGGL(k_fb_finalize_cost, dim3(1), dim3(kFbCostThreads), 0, st, cpart, ncpart,
                        r.M, p.dt, g != nullptr ? p.gsq : nullptr, fb_gsq_count(p), J_out, hdr, slot,
-                       gate);
+                       gate, tail);
     return hipGetLastError();
 }
 

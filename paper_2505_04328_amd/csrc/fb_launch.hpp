@@ -32,6 +32,12 @@ struct FbHost {
     uint64_t thr[32];     // Poisson(rate dt) thresholds
     PoissonTable poisson;
     void* small;          // the workspace's scratch of the small-count kernels (FbSmall)
+    // Line search: the step that follows this evaluation (null: none).  With an
+    // Armijo step the evaluation is of its trial points mu - zeta[i] ls_g, written
+    // to ls_ut (N L values each), i < ls->trials <= fb_trials().
+    const LsTail* ls = nullptr;
+    const double* ls_g = nullptr;
+    double* ls_ut = nullptr;
     double* gsq;          // the workspace's sums of squares of the gradient (fb_gsq_count())
 };
 
@@ -76,6 +82,14 @@ struct FbRowPlan {
 };
 // The split of a sweep over workgroups of `slots` particles.
 FbRowPlan fb_row_plan(const FbHost& p, const HostRun& r, int slots);
+
+// Line-search trials evaluated together: forwards side by side while they leave the
+// chip idle, each with its own table (fb_table_layout().count elements) and
+// costs (fb_forward_blocks()).
+int fb_trials(const FbHost& p, const HostRun& r);
+inline int fb_trials_of(const FbHost& p) {
+    return p.ls != nullptr && p.ls->mode == kLsTailArmijo ? p.ls->trials : 1;
+}
 
 hipError_t fb_launch_table(const FbHost& p, const HostRun& r, const double* mu, void* tab,
                            WsHeader* hdr, int clear_flag, hipStream_t st, Gate gate = kNoGate);

@@ -65,6 +65,9 @@ struct FbRows {
     Real* in;         // x, v, cx, cv of every particle at k0 (k0 > 0)
     Real* out;        // the same at k1 (k1 < N)
     double* acc;      // running cost of every particle
+    // independent particles, cost only: grid row y evaluates trial y of a line
+    // search, with its own table and costs
+    int64_t tab, costs;
 };
 
 // Slot q of a ring workgroup of SL slots: own = 0: `rings` whole rings per
@@ -122,6 +125,12 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
                   FbRows<Real> f) {
     if (gate_closed(a.gate))
         return;
+    if constexpr (!STORE && !RING) {
+        mu += blockIdx.y * f.tab;
+        zd += blockIdx.y * f.tab;
+        ks += blockIdx.y * f.tab;
+        cpart += blockIdx.y * f.costs;
+    }
     constexpr int SL = TPB / 16;
     constexpr int WS = fb_row_stride(W);
     constexpr int NP = (16 * W * W + TPB - 1) / TPB;
@@ -300,9 +309,14 @@ template <typename Real, int W, bool STORE>
 __global__ void __launch_bounds__(16 * kFbRowSlots)
 k_fb_forward_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
                           const Real* __restrict__ zd, void* traj, double* __restrict__ cpart,
-                          int nvp) {
+                          int nvp, int64_t tab, int64_t costs) {
     if (gate_closed(a.gate))
         return;
+    if constexpr (!STORE) {  // trial y of a line search (FbRows)
+        mu += blockIdx.y * tab;
+        zd += blockIdx.y * tab;
+        cpart += blockIdx.y * costs;
+    }
     constexpr int TPB = 16 * kFbRowSlots;
     constexpr int WS = fb_row_stride(W);
     constexpr int NP = (16 * W * W + TPB - 1) / TPB;
@@ -987,10 +1001,12 @@ hipError_t fb_small_forward(const FbHost& p, const HostRun& r, const void* tab, 
     const Real* tb = (const Real*)tab;
     const FbSmall sm = fb_small_layout(p, r);
     const FbRowPlan pl = fb_row_plan(p, r, fb_row_slots(p));
+    const dim3 grid((unsigned)pl.blocks, (unsigned)fb_trials_of(p));
     if (p.grid == 1) {
 #define FB_ROWS_A(W, S)                                                                           \
-    hipLaunchKernelGGL((k_fb_forward_adapted_rows<Real, W, S>), dim3((unsigned)pl.blocks),        \
-                       dim3(16 * kFbRowSlots), 0, st, a, tb + t.mu, tb + t.zd, traj, cpart, p.nvp)
+    hipLaunchKernelGGL((k_fb_forward_adapted_rows<Real, W, S>), grid, dim3(16 * kFbRowSlots), 0,  \
+                       st, a, tb + t.mu, tb + t.zd, traj, cpart, p.nvp, (int64_t)t.count,         \
+                       pl.blocks)
         if (p.nx <= 10 && p.nv <= 10) {
             if (traj != nullptr) FB_ROWS_A(10, true);
             else FB_ROWS_A(10, false);
@@ -1004,6 +1020,8 @@ hipError_t fb_small_forward(const FbHost& p, const HostRun& r, const void* tab, 
     FbRows<Real> f = fb_rows<Real>(p, pl);
     Real* state = (Real*)((char*)p.small + sm.state);
     f.acc = (double*)((char*)p.small + sm.acc);
+    f.tab = (int64_t)t.count;
+    f.costs = pl.blocks;
     for (int k0 = 0, c = 0; k0 < p.N; k0 += pl.steps, ++c) {
         f.k0 = k0;
         f.k1 = p.N - k0 < pl.steps ? p.N : k0 + pl.steps;
@@ -1012,8 +1030,8 @@ hipError_t fb_small_forward(const FbHost& p, const HostRun& r, const void* tab, 
         f.in = state + (size_t)(c & 1) * 4 * r.M;
         f.out = state + (size_t)((c + 1) & 1) * 4 * r.M;
 #define FB_ROWS(W, S, RG, TPB)                                                                    \
-    hipLaunchKernelGGL((k_fb_forward_rows<Real, W, S, RG, TPB>), dim3((unsigned)pl.blocks),       \
-                       dim3(TPB), 0, st, a, tb + t.mu, tb + t.zd, tb + t.ks, traj, cpart, f)
+    hipLaunchKernelGGL((k_fb_forward_rows<Real, W, S, RG, TPB>), grid, dim3(TPB), 0, st, a,       \
+                       tb + t.mu, tb + t.zd, tb + t.ks, traj, cpart, f)
 #define FB_ROWS_R(W, S)                                                                           \
     do {                                                                                          \
         if (p.np == 1) FB_ROWS(W, S, false, 16 * kFbRowSlots);                                    \

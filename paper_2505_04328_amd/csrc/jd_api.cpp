@@ -251,8 +251,6 @@ int LsDriver::enqueue(LsOps& ops, int iters, hipStream_t st) {
             tg.n = n;
             if ((rc = ops.grad(n, tg, gate_of(hdr, ls_phase(n, -1)), st)))
                 return rc;
-            if (!ops.fused())
-                JD_TRY(launch_ls_after_grad(hdr, n, st));
             j0 = 0;
         }
         // zeta_j = zeta0 rho^j by repeated multiplication, as one trial at a time
@@ -260,10 +258,9 @@ int LsDriver::enqueue(LsOps& ops, int iters, hipStream_t st) {
         for (int j = 0; j < j0; ++j)
             zeta *= opt.rho;
         const int jend = opt.max_backtracks - j0 < ahead ? opt.max_backtracks : j0 + ahead;
-        for (int j = j0; j < jend; ++j) {
+        for (int j = j0; j < jend;) {
             LsArmijo a;
             a.c_armijo = opt.c_armijo;
-            a.zeta = zeta;
             a.dt = dt;
             a.tol = opt.tol;
             a.n = n;
@@ -274,16 +271,17 @@ int LsDriver::enqueue(LsOps& ops, int iters, hipStream_t st) {
             LsTail ta{};
             ta.mode = kLsTailArmijo;
             ta.n = n;
+            ta.trials = jend - j < ops.trials() ? jend - j : ops.trials();
+            for (int i = 0; i < ta.trials; ++i, zeta *= opt.rho)
+                ta.zeta[i] = zeta;
             ta.ls = a;
             ta.ring = ring;
             ta.u = u;
             ta.ut = ut;
             ta.nd = nd;
-            if ((rc = ops.trial(n, zeta, ta, gate_of(hdr, ls_phase(n, j)), st)))
+            if ((rc = ops.trial(n, ta, gate_of(hdr, ls_phase(n, j)), st)))
                 return rc;
-            if (!ops.fused())
-                JD_TRY(launch_armijo(hdr, ring, u, ut, nd, a, st));
-            zeta *= opt.rho;
+            j += ta.trials;
         }
         j0 = -1;
     }
@@ -336,12 +334,11 @@ struct JdOps : LsOps {
         rn.iter = r.iter + (uint32_t)n;
         return enqueue_cost_grad(p, rn, u, nullptr, w.gbuf, traj, w, st, gate, &tail);
     }
-    int trial(int n, double zeta, const LsTail& tail, Gate gate, hipStream_t st) override {
+    int trial(int n, const LsTail& tail, Gate gate, hipStream_t st) override {
         HostRun rn = r;
         rn.iter = r.iter + (uint32_t)n;
-        return enqueue_trial(p, rn, u, zeta, w, st, gate, &tail);
+        return enqueue_trial(p, rn, u, tail.zeta[0], w, st, gate, &tail);
     }
-    bool fused() const override { return true; }
 };
 
 }  // namespace

@@ -166,9 +166,10 @@ FbLayout fb_layout(const FbHost& p, const HostRun& r) {
     L.ring = off;
     off += round_up(kLsLogCap * sizeof(LsLog), kAlign);
     L.tab = off;
-    off += round_up(fb_table_layout(p).count * real_size(r.prec), kAlign);
+    const size_t nt = (size_t)fb_trials(p, r);
+    off += round_up(nt * fb_table_layout(p).count * real_size(r.prec), kAlign);
     L.cpart = off;
-    const int fwd = fb_forward_blocks(p, r);
+    const int fwd = (int)nt * fb_forward_blocks(p, r);
     off += round_up((size_t)(r.nblk > fwd ? r.nblk : fwd) * sizeof(double), kAlign);
     L.apart = off;
     off += round_up((size_t)r.nblk * p.N * p.L * sizeof(double), kAlign);
@@ -177,7 +178,7 @@ FbLayout fb_layout(const FbHost& p, const HostRun& r) {
     L.gsq = off;
     off += round_up((size_t)fb_gsq_count(p) * sizeof(double), kAlign);
     L.ut = off;
-    off += round_up((size_t)p.N * p.L * sizeof(double), kAlign);
+    off += round_up(nt * p.N * p.L * sizeof(double), kAlign);
     // surrogate gradient: the forward's per-step moment partials (fitted
     // variance only), the per-step variance and the variance line
     L.mom = off;
@@ -254,12 +255,10 @@ int fb_enqueue_cost_grad(const FbHost& p, const HostRun& r, const double* mu, do
     return JD_OK;
 }
 
-// Trial point mu - zeta g and its cost into the header's J_trial, under gate.
-int fb_enqueue_trial(const FbHost& p, const HostRun& r, const double* mu, double zeta,
-                     const FbWs& w, hipStream_t st, Gate gate) {
-    const int nl = p.N * p.L;
-    JD_TRY(launch_trial(mu, w.gbuf, zeta, w.ut, nl, st, gate));
-    JD_TRY(fb_launch_table(p, r, w.ut, w.tab, w.hdr, 0, st, gate));
+// The trial points p.ls, their costs and Armijo tests, under gate.
+int fb_enqueue_trial(const FbHost& p, const HostRun& r, const double* mu, const FbWs& w,
+                     hipStream_t st, Gate gate) {
+    JD_TRY(fb_launch_table(p, r, mu, w.tab, w.hdr, 0, st, gate));
     JD_TRY(fb_launch_forward(p, r, w.tab, nullptr, w.cpart, w.hdr, st, gate));
     JD_TRY(fb_launch_finalize_cost(p, r, w.cpart, fb_forward_blocks(p, r), nullptr, nullptr, w.hdr,
                                    1, st, gate));
@@ -274,16 +273,25 @@ struct FbOps : LsOps {
     const FbWs& w;
     FbOps(const FbHost& p_, const HostRun& r_, const double* mu_, void* traj_, const FbWs& w_)
         : p(p_), r(r_), mu(mu_), traj(traj_), w(w_) {}
-    int grad(int n, const LsTail&, Gate gate, hipStream_t st) override {
+    // the problem with the line-search step that follows its evaluation
+    FbHost with(const LsTail& tail) const {
+        FbHost q = p;
+        q.ls = &tail;
+        q.ls_g = w.gbuf;
+        q.ls_ut = w.ut;
+        return q;
+    }
+    int grad(int n, const LsTail& tail, Gate gate, hipStream_t st) override {
         HostRun rn = r;
         rn.iter = r.iter + (uint32_t)n;
-        return fb_enqueue_cost_grad(p, rn, mu, nullptr, w.gbuf, traj, w, st, gate);
+        return fb_enqueue_cost_grad(with(tail), rn, mu, nullptr, w.gbuf, traj, w, st, gate);
     }
-    int trial(int n, double zeta, const LsTail&, Gate gate, hipStream_t st) override {
+    int trial(int n, const LsTail& tail, Gate gate, hipStream_t st) override {
         HostRun rn = r;
         rn.iter = r.iter + (uint32_t)n;
-        return fb_enqueue_trial(p, rn, mu, zeta, w, st, gate);
+        return fb_enqueue_trial(with(tail), rn, mu, w, st, gate);
     }
+    int trials() const override { return fb_trials(p, r); }
 };
 
 }  // namespace
@@ -390,6 +398,8 @@ int jd_fb_optimize(const jd_fb_problem* prob, const jd_run* run, const jd_opt* o
     drv.dt = p.dt;
     drv.iter0 = r.iter;
     FbOps ops(p, r, mu, traj, w);
+    if (drv.ahead < ops.trials())
+        drv.ahead = ops.trials();
     alignas(16) char mirror[kLsMirrorBytes];
     if ((rc = drv.start(stream)))
         return rc;

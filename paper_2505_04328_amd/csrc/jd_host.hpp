@@ -94,17 +94,18 @@ int enqueue_trial(const HostProblem& p, const HostRun& r, const double* u, doubl
 // the header and the log ring (one synchronization or event per batch), and
 // resumes where the device stopped: at the next iteration, or at the next
 // trial of an iteration that needed more trials than were enqueued.  The
-// arithmetic and its order are those of one trial at a time.
+// arithmetic and its order are those of one trial at a time, also where the model
+// evaluates several trials together (trials()).
 struct LsOps {
     virtual ~LsOps() {}
-    // J(u^n), g^n with counter word iter0 + n, under gate; tail: the
-    // after-gradient step, which fused() evaluations run themselves
+    // J(u^n), g^n with counter word iter0 + n, under gate, then tail, the
+    // after-gradient step
     virtual int grad(int n, const LsTail& tail, Gate gate, hipStream_t st) = 0;
-    // trial point and cost of iteration n at step zeta, under gate; tail: the
-    // Armijo test, which fused() trials run themselves
-    virtual int trial(int n, double zeta, const LsTail& tail, Gate gate, hipStream_t st) = 0;
-    // the tails run inside grad() and trial() (no launches of their own)
-    virtual bool fused() const { return false; }
+    // trial points and costs of iteration n at the steps tail.zeta[], under
+    // gate, then tail, their Armijo tests
+    virtual int trial(int n, const LsTail& tail, Gate gate, hipStream_t st) = 0;
+    // trials evaluated together, at most kLsTrials
+    virtual int trials() const { return 1; }
 };
 
 struct LsDriver {

@@ -11,7 +11,7 @@
 //                     segment with the same counters (bit-identical states)
 //  k_finalize_grad    fixed-order FP64 sum of the per-block partials -> g
 //  k_finalize_cost    fixed-order FP64 sum of the path costs -> J, ||g||^2
-//  k_trial, k_armijo  line-search step and sufficient-decrease test
+//                     and the line-search step that follows (jd_linesearch.hpp)
 //  k_draws, k_philox  the draws / raw Philox words, for parity checks
 //
 // The paper's method: forward model (Section 3, eq. model_approximation;
@@ -20,6 +20,7 @@
 // (Section 5, eq. Stochastic_Armijo, Algorithm 5.4).
 #include "jd_device.hpp"
 #include "jd_launch.hpp"
+#include "jd_linesearch.hpp"
 
 namespace jd {
 
@@ -1098,85 +1099,6 @@ k_finalize_grad(const double* __restrict__ part, int nblk, int D, int d, int64_t
     finalize_grad_step(part, nblk, D, d, M, nu, u, B, g, hdr, blockIdx.x, sh, G);
 }
 
-// Sufficient decrease J(u - zeta g) <= J(u) - c zeta ||g||^2_L2 on the same
-// draws (a non-finite trial cost is rejected); on acceptance records
-// ||u' - u||^2_L2, moves u to u', writes the iteration's log entry and opens
-// the next phase of the device-driven iteration (see LsArmijo).  All threads
-// of one block; sh: kThreads doubles of LDS.
-__device__ __forceinline__ void armijo_step(WsHeader* hdr, LsLog* __restrict__ ring,
-                                            double* __restrict__ u, const double* __restrict__ ut,
-                                            int nd, const LsArmijo& ls, double* sh) {
-    __shared__ int acc;
-    if (threadIdx.x == 0) {
-        const double J = hdr->J, Jt = hdr->J_trial;
-        acc = (isfinite(Jt) && Jt <= J - ls.c_armijo * ls.zeta * hdr->gnorm2) ? 1 : 0;
-        hdr->accept = acc;
-    }
-    __syncthreads();
-    if (!acc) {
-        if (threadIdx.x == 0) {
-            if (ls.j + 1 >= ls.max_backtracks) {
-                hdr->ls_status = JD_ELINESEARCH;
-                hdr->ls_phase = kLsStop;
-            } else {
-                hdr->ls_phase = ls_phase(ls.n, ls.j + 1);
-            }
-        }
-        return;
-    }
-    double e = 0.0;
-    for (int q = threadIdx.x; q < nd; q += kThreads) {
-        const double r = ut[q] - u[q];
-        e += r * r;
-    }
-    e = block_sum(e, sh);
-    for (int q = threadIdx.x; q < nd; q += kThreads)
-        u[q] = ut[q];
-    if (threadIdx.x == 0) {
-        const double E2 = ls.dt * e;
-        hdr->E2 = E2;
-        LsLog& L = ring[ls.n % kLsLogCap];
-        L.J = hdr->J;
-        L.gnorm2 = hdr->gnorm2;
-        L.zeta = ls.zeta;
-        L.J_new = hdr->J_trial;
-        L.E2 = E2;
-        L.iter = ls.iter;
-        L.backtracks = ls.j;
-        L.n = ls.n;
-        hdr->ls_done = ls.n + 1;
-        if (ls.n + 1 >= ls.n_max || sqrt(E2) <= ls.tol) {
-            hdr->ls_status = kLsDone;
-            hdr->ls_phase = kLsStop;
-        } else {
-            hdr->ls_phase = ls_phase(ls.n + 1, -1);
-        }
-    }
-}
-
-// Gated by the phase of trial (ls.n, ls.j).
-__global__ void __launch_bounds__(kThreads)
-k_armijo(WsHeader* hdr, LsLog* __restrict__ ring, double* __restrict__ u,
-         const double* __restrict__ ut, int nd, LsArmijo ls) {
-    if (hdr->ls_phase != ls_phase(ls.n, ls.j))
-        return;
-    __shared__ double sh[kThreads];
-    armijo_step(hdr, ring, u, ut, nd, ls, sh);
-}
-
-// After the gradient of iteration n (one thread): on to trial (n, 0), or stop
-// with JD_ENONFINITE.
-__device__ __forceinline__ void ls_after_grad_step(WsHeader* hdr, int n) {
-    if (hdr->ls_phase == ls_phase(n, -1)) {
-        if (hdr->nonfinite) {
-            hdr->ls_status = JD_ENONFINITE;
-            hdr->ls_phase = kLsStop;
-        } else {
-            hdr->ls_phase = ls_phase(n, 0);
-        }
-    }
-}
-
 // J = (1/M) sum C + nu dt/2 sum |u|^2, and if g is given also dt sum |g|^2
 // (one block); flags non-finite results, then runs the line-search tail.
 __device__ __forceinline__ void finalize_cost_block(const double* __restrict__ cpart, int nblk,
@@ -1220,8 +1142,10 @@ __device__ __forceinline__ void finalize_cost_block(const double* __restrict__ c
             ls_after_grad_step(hdr, tail.n);
     }
     if (tail.mode == kLsTailArmijo) {
-        __syncthreads();
-        armijo_step(hdr, tail.ring, tail.u, tail.ut, tail.nd, tail.ls, sh);
+        __shared__ double Jt;
+        if (threadIdx.x == 0)
+            Jt = hdr->J_trial;
+        armijo_step<kThreads>(hdr, tail, &Jt, sh);
     }
 }
 
@@ -1235,16 +1159,6 @@ k_finalize_cost(const double* __restrict__ cpart, int nblk, int64_t M, double nu
     finalize_cost_block(cpart, nblk, M, nu, dt, u, g, nd, J_out, hdr, slot, tail, sh);
 }
 
-__global__ void __launch_bounds__(kThreads)
-k_trial(const double* __restrict__ u, const double* __restrict__ g, double zeta,
-        double* __restrict__ ut, int nd, Gate gate) {
-    if (gate_closed(gate))
-        return;
-    const int q = blockIdx.x * kThreads + threadIdx.x;
-    if (q < nd)
-        ut[q] = u[q] - zeta * g[q];
-}
-
 __global__ void k_ls_start(WsHeader* hdr) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         hdr->nonfinite = 0;
@@ -1253,13 +1167,6 @@ __global__ void k_ls_start(WsHeader* hdr) {
         hdr->ls_phase = ls_phase(0, -1);
         hdr->ls_done = 0;
     }
-}
-
-// After the evaluation of J(u^n), g^n: stop on a non-finite result, else
-// open the first trial.
-__global__ void k_ls_after_grad(WsHeader* hdr, int n) {
-    if (threadIdx.x == 0 && blockIdx.x == 0)
-        ls_after_grad_step(hdr, n);
 }
 
 __global__ void k_clear_flag(WsHeader* hdr) {
@@ -1609,26 +1516,8 @@ hipError_t launch_finalize_cost(const HostProblem& p, const HostRun& r, const do
     return hipGetLastError();
 }
 
-hipError_t launch_trial(const double* u, const double* g, double zeta, double* ut, int nd,
-                        hipStream_t st, Gate gate) {
-    hipLaunchKernelGGL(k_trial, dim3(blocks_for(nd)), dim3(kThreads), 0, st, u, g, zeta, ut, nd,
-                       gate);
-    return hipGetLastError();
-}
-
-hipError_t launch_armijo(WsHeader* hdr, LsLog* ring, double* u, const double* ut, int nd,
-                         const LsArmijo& ls, hipStream_t st) {
-    hipLaunchKernelGGL(k_armijo, dim3(1), dim3(kThreads), 0, st, hdr, ring, u, ut, nd, ls);
-    return hipGetLastError();
-}
-
 hipError_t launch_ls_start(WsHeader* hdr, hipStream_t st) {
     hipLaunchKernelGGL(k_ls_start, dim3(1), dim3(64), 0, st, hdr);
-    return hipGetLastError();
-}
-
-hipError_t launch_ls_after_grad(WsHeader* hdr, int n, hipStream_t st) {
-    hipLaunchKernelGGL(k_ls_after_grad, dim3(1), dim3(64), 0, st, hdr, n);
     return hipGetLastError();
 }
 

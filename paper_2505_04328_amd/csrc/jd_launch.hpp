@@ -172,21 +172,25 @@ hipError_t launch_finalize_grad(const HostProblem& p, const HostRun& r, const do
 // (n + 1 == n_max, or ||u' - u||_L2 <= tol); on rejection it opens (n, j + 1)
 // or stops with JD_ELINESEARCH after max_backtracks trials.
 struct LsArmijo {
-    double c_armijo, zeta, dt, tol;
+    double c_armijo, dt, tol;
     int n, j, n_max, max_backtracks;
     uint32_t iter;
 };
 
 // A line-search step run by the cost reduction that precedes it
 // (launch_finalize_cost), in place of its own launch: the after-gradient step
-// of iteration n, or the Armijo test of a trial (ring, u, ut, nd as for
-// launch_armijo).  The reduction's gate is the step's phase.
+// of iteration n, or the Armijo tests of trials ls.j .. ls.j + trials - 1 of step
+// sizes zeta[], evaluated together (trial points at ut, nd values each).  The
+// reduction's gate is the step's (first trial's) phase.
+constexpr int kLsTrials = 4;
 constexpr int kLsTailNone = 0;
 constexpr int kLsTailAfterGrad = 1;
 constexpr int kLsTailArmijo = 2;
 struct LsTail {
     int mode;
     int n;
+    int trials;
+    double zeta[kLsTrials];
     LsArmijo ls;
     LsLog* ring;
     double* u;
@@ -202,18 +206,13 @@ hipError_t launch_finalize_cost(const HostProblem& p, const HostRun& r, const do
                                 const double* u, const double* g, double* J_out, WsHeader* hdr,
                                 int slot, hipStream_t st, Gate gate = kNoGate,
                                 const LsTail* tail = nullptr);
-hipError_t launch_trial(const double* u, const double* g, double zeta, double* ut, int nd,
-                        hipStream_t st, Gate gate = kNoGate);
-// launch_trial and launch_setup(ut) in one launch: ut = u - zeta g and the
-// per-step table of ut (no flag clearing), bitwise the two launches' results.
+// The trial point ut = u - zeta g and launch_setup(ut) in one launch (no flag
+// clearing).
 hipError_t launch_setup_trial(const HostProblem& p, const HostRun& r, const double* u,
                               const double* g, double zeta, double* ut, void* tab, WsHeader* hdr,
                               hipStream_t st, Gate gate = kNoGate);
 
 hipError_t launch_ls_start(WsHeader* hdr, hipStream_t st);
-hipError_t launch_ls_after_grad(WsHeader* hdr, int n, hipStream_t st);
-hipError_t launch_armijo(WsHeader* hdr, LsLog* ring, double* u, const double* ut, int nd,
-                         const LsArmijo& ls, hipStream_t st);
 hipError_t launch_draws(const HostProblem& p, const HostRun& r, int64_t m0, int64_t mc, int k0,
                         int kc, void* zw, void* zj, int32_t* counts, hipStream_t st);
 hipError_t launch_philox(uint64_t seed, const uint32_t* ctr, int64_t n, uint32_t* out,
