@@ -206,6 +206,18 @@ __device__ __forceinline__ Real row_dot(const Real (&m)[W], Real pv, Real t) {
     return t;
 }
 
+// acc + p of lane 0 + q of lane 0 + p of lane 1 + ... (16 lanes, in that order).
+#define JD_ROW_PAIR(i)                                                                            \
+    "v_fmac_f64_dpp %0, %1, %3" JD_ROW_DPP(i) "v_fmac_f64_dpp %0, %2, %3" JD_ROW_DPP(i)
+__device__ __forceinline__ double row_add_pairs(double p, double q, double acc) {
+    asm("s_nop 1\n\t" JD_ROW_PAIR(0) JD_ROW_PAIR(1) JD_ROW_PAIR(2) JD_ROW_PAIR(3) JD_ROW_PAIR(4)
+        JD_ROW_PAIR(5) JD_ROW_PAIR(6) JD_ROW_PAIR(7) JD_ROW_PAIR(8) JD_ROW_PAIR(9) JD_ROW_PAIR(10)
+        JD_ROW_PAIR(11) JD_ROW_PAIR(12) JD_ROW_PAIR(13) JD_ROW_PAIR(14) JD_ROW_PAIR(15)
+        : "+v"(acc)
+        : "v"(p), "v"(q), "v"(1.0));
+    return acc;
+}
+
 // sum_i (b of lane i) (t of lane i), i = 0 .. W-1 in order; p, q: scratch.
 #define JD_ROW_SUM2(F, B, i, j)                                                                   \
     "v_mov_" B "_dpp %1, %4" JD_ROW_DPP(i) "v_mov_" B "_dpp %2, %4" JD_ROW_DPP(j)                 \

@@ -24,8 +24,8 @@
 // sums differs.
 //
 // Measured (MI355X): 2000 particles x 50 steps of the 10 x 10 grid, FP32:
-// forward 127 -> 30 us, adjoint 109 -> 18 us (5.5 + 8.2 + 4.4); one FP64 ring of
-// 2000 x 50: 1055 -> 75 us (four launches) and 1015 -> 39 us (10 + 20 + 8.4).  Jump-adapted
+// forward 127 -> 21 us, adjoint 109 -> 18 us (5.5 + 8.2 + 4.4); one FP64 ring of
+// 2000 x 50: 1055 -> 62 us (four launches) and 1015 -> 39 us (10 + 20 + 8.4).  Jump-adapted
 // grid, 2000 x 50: forward 214 -> 68 us, adjoint 364 -> 65 us (FP64 679 -> 93, 672 -> 86).
 #include "fb_device.hpp"
 
@@ -44,11 +44,11 @@ __device__ __forceinline__ Real row_control(const FbArgs<Real>& a, const Real (&
     return row_sum<Real, W>(bx, t);
 }
 
-// Draws of one step: the Box-Muller cosine and sine branches, the jump normal
-// and the count (kept as a Real: one 16- or 32-byte LDS read brings all four).
+// Draws of one step: the Box-Muller cosine and sine branches, and the step's jumps
+// v <- gn v + sv zj (without jumps gn = 1 and sv zj = -0, which leaves v as it is).
 template <typename Real>
 struct alignas(4 * sizeof(Real)) FbRowDraw {
-    Real zc, zs, zj, n;
+    Real zc, zs, zj, sv, gn, pad[3];
 };
 
 // Row of a step's coefficients in LDS, padded to 16-byte reads.
@@ -118,6 +118,12 @@ __device__ __forceinline__ FbRingSlot fb_ring_slot(const FbArgs<Real>& a, int ow
 // one slot inward in two steps: after T <= 2 halo steps the own slots are
 // still exact.  A launch runs those T steps and hands the own particles' state
 // to the next launch.
+//
+// Bound by a step's chain of dependent operations, so what does not feed the next
+// state is done for 16 steps at once, a step per lane: the draws and jump factors
+// before the batch, the costs, stores and dumps after it; a step's LDS reads are
+// issued during the step before.  2000 particles x 50: 44.6 -> 35.8 us (FP64 59 ->
+// 44), 32768: 111 -> 88 (228 -> 156), one FP64 ring of 2000: 85 -> 78.
 template <typename Real, int W, bool STORE, bool RING, int TPB>
 __global__ void __launch_bounds__(TPB)
 k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
@@ -172,6 +178,7 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
         tcnt = (uint8_t*)((Real*)traj + (size_t)a.nblk * (a.N + 1) * 2 * kThreads) +
                (size_t)b * a.N * kThreads + l;
     }
+    // the state at k: lane j < 2 stores its component
     auto put = [&](int k) {
         if (STORE && keep && j < 2)
             trow[((size_t)k * 2 + j) * kThreads] = j == 0 ? x : v;
@@ -212,6 +219,7 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
         }
         if (kb + 16 < f.k1)
             fetch(kb + 16);
+        int n;
         {
             // lane j: the draws of step kb + j
             uint32_t w[4];
@@ -221,24 +229,34 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
             FbRowDraw<Real> d;
             d.zc = bm_cos(R, ub, a.dtab);
             d.zs = bm_sin(R, ub, a.dtab);
-            d.zj = 0;
-            const int n = poisson_count(poisson_word(w), a.thr0, a.thr);
-            if (n != 0)
+            d.zj = (Real)-0.0;
+            d.sv = 0;
+            d.gn = 1;
+            n = poisson_count(poisson_word(w), a.thr0, a.thr);
+            if (n != 0) {
                 d.zj = bm_cos(bm_radius(w[2], (Real)0, a.dtab), bm_angle<Real>(w[3]), a.dtab);
-            d.n = (Real)n;
+                ks_factors(ks, n, d.gn, d.sv);
+            }
             dr[row][j] = d;
         }
-        lds_barrier();
         const int ns = f.k1 - kb < 16 ? f.k1 - kb : 16;
-        for (int s = 0; s < ns; ++s) {
-            const int k = kb + s;
-            const FbRowDraw<Real> d = dr[row][s];
-            if (RING && j == 0)
-                xs[k & 1][row] = x;
-            Real m[W];
+        Real z[2] = {0, 0};
+        if (j < ns) {
+            z[0] = zd[2 * (kb + j + 1)];
+            z[1] = zd[2 * (kb + j + 1) + 1];
+        }
+        lds_barrier();
+        Real hx = 0, hv = 0, hu = 0;  // lane j: state and control of step kb + j
+        auto load = [&](int s, Real (&m)[W], FbRowDraw<Real>& d) {
+            d = dr[row][s];
 #pragma unroll
             for (int l = 0; l < W; ++l)
                 m[l] = mus[s][j < W ? j : 0][l];
+        };
+        auto step = [&](int s, const Real (&m)[W], const FbRowDraw<Real>& d) {
+            const int k = kb + s;
+            if (RING && j == 0)
+                xs[k & 1][row] = x;
             Real cpl = 0;
             const Real u = row_control<Real, W>(a, m, j, x, v);
             if (RING) {
@@ -254,22 +272,42 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
                 xn = fma(a.sqb1, d.zc, fma(a.dt, v, x));
                 vs = fma(a.sqb2, d.zs, fma(a.dt, fma(-a.eta, x, u) - cpl, v));
             }
-            if (d.n != (Real)0) {
-                Real gn, sv;
-                ks_factors(ks, (int)d.n, gn, sv);
-                vs = fma(sv, d.zj, gn * vs);
-                ev = gn * ev;
-            }
             x = xn;
-            v = vs;
+            v = fma(d.sv, d.zj, d.gn * vs);
             cx = ex;
-            cv = ev;
-            acc += (double)(a.hadt * u * u);
-            acc += (double)(a.dt * track(a, x, v, zd + 2 * (k + 1)));
-            put(k + 1);
-            if (STORE && keep && j == 2)
-                tcnt[(size_t)k * kThreads] = (uint8_t)(int)d.n;
+            cv = d.gn * ev;
+            const bool mine = j == s;
+            hx = mine ? x : hx;
+            hv = mine ? v : hv;
+            hu = mine ? u : hu;
+        };
+        // a step's LDS reads are issued during the step before
+        Real ma[W], mb[W];
+        FbRowDraw<Real> da, db;
+        load(0, ma, da);
+        for (int s = 0; s < ns; s += 2) {
+            load(s + 1, mb, db);
+            step(s, ma, da);
+            load(s + 2 < 16 ? s + 2 : 15, ma, da);
+            if (s + 1 < ns)
+                step(s + 1, mb, db);
         }
+        // costs, states and counts of the batch's steps, one step per lane; the
+        // costs are added in the steps' order
+        double tu = 0.0, tz = 0.0;
+        if (j < ns) {
+            tu = (double)(a.hadt * hu * hu);
+            tz = (double)(a.dt * track(a, hx, hv, z));
+            const int k = kb + j;
+            if (STORE && keep) {
+                trow[((size_t)(k + 1) * 2) * kThreads] = hx;
+                trow[((size_t)(k + 1) * 2 + 1) * kThreads] = hv;
+                tcnt[(size_t)k * kThreads] = (uint8_t)n;
+            }
+            if (act)
+                fb_dump(a, a.dX, k + 1, p, hx, hv);
+        }
+        acc = row_add_pairs(tu, tz, acc);
     }
     if (f.k1 < a.N) {
         if (act && j < 4)

@@ -78,19 +78,21 @@ int fb_ring_groups(int np) { return np <= kBlock ? 1 : 8; }
 // Forward: a row kernel's time grows with the slots it computes (a segment's
 // halos included), the lane kernels' stays flat up to one wave per SIMD
 // (65536 particles) and, for rings of more than 256 particles, one workgroup per
-// CU.  Row / lane, FP32: 44 / 141 us at 2000 particles, 111 / 134 at 32768,
-// 189 / 136 at 65536; FP64 58 / 276, 228 / 257, 431 / 261.  Rings of 8..256, by
-// computed slots: FP32 130 / 147 at 32000, 234 / 147 at 71680; FP64 155 / 268 at
-// 8960, 296 / 270 at 32000.  Rings of 500 and 2000: FP32 298 / 334 at 96000, 329 /
-// 334 at 128000; FP64 827 / 1080 at 96000.  Jump-adapted grid (0.18 jumps per
+// CU.  Row / lane, FP32: 36 / 144 us at 2000 particles, 117 / 134 at 49152, 132 / 134
+// at 57344; FP64 42 / 250, 224 / 242, 255 / 242.  Rings of 8..256, by computed slots:
+// FP32 114 / 144 at 26900, 155 / 144 at 47600, 174 / 144 at 53800; FP64 182 / 242 at 23600, 336 /
+// 242 at 47100.  Rings of 500 and 2000: FP32 267 / 334 at 96000, 345 / 334 at 128000;
+// FP64 850 / 1084 at 128000, 1054 / 1084 at 160000.  Jump-adapted grid (0.18 jumps per
 // interval): FP32 68 / 205 at 2000, 159 / 199 at 28672, 198 / 199 at 32768 (at 0.93
 // per interval 235 / 232); FP64 93 / 488 at 2000, 380 / 488 at 32768, 478 / 488 at 40960.
 static int64_t fb_small_forward_max(const FbHost& p, const HostRun& r) {
     if (p.np > 1 && p.G > 1)
-        return 98304;
+        return r.prec == JD_FP64 ? 147456 : 114688;
     if (p.grid == 1)
         return r.prec == JD_FP64 ? 32768 : 28672;
-    return p.np > 1 && r.prec == JD_FP64 ? 24576 : 32768;
+    if (p.np > 1)
+        return r.prec == JD_FP64 ? 32768 : 40960;
+    return 49152;
 }
 // Adjoint, split / one kernel: FP32 33 / 162 us at 2000 particles, 72 / 163 at
 // 32768, 118 / 169 at 65536 (the whole gradient 260 / 267), 171 / 172 at 100000 (309 /
@@ -134,8 +136,8 @@ bool fb_small_forward_ok(const FbHost& p, const HostRun& r) {
 }
 
 // A row forward's time hardly grows up to 8192 particles (50 steps, the whole call: FP32
-// 45 us at 2000 particles, 48 at 8192, 54 at 12288, FP64 59 / 66 / 83; jump-adapted
-// grid 67 / 78 / 88 and 93 / 119 / 169), so up to four trials of a line search share one
+// 36 us at 2000 particles, 42 at 8192, 57 at 16384, FP64 43 / 58 / 91; jump-adapted
+// grid 67 / 78 / 105 and 93 / 119 / 209), so up to four trials of a line search share one
 // launch.  Ten iterations of 2000 particles x 50 on the jump-adapted grid, 28 trials:
 // 3.78 ms with a launch per trial, 2.16 with four in one.
 int fb_trials(const FbHost& p, const HostRun& r) {
