@@ -1057,29 +1057,42 @@ k_adjoint_segments(SweepArgs<Real, D> a, const Real* __restrict__ tab, Real* __r
 }
 
 // ---------------------------------------------------------------------------
-// Step k's gradient (one block): sums the d rows (k, c) of block partials in
-// a fixed order, then g_k = nu u_k + B^T (sum / M); a non-finite entry raises
-// the flag.  sh: kThreads doubles of LDS, G: 8.
-__device__ __forceinline__ void finalize_grad_step(const double* __restrict__ part, int nblk,
-                                                   int D, int d, int64_t M, double nu,
-                                                   const double* __restrict__ u, const BMat& B,
-                                                   double* g, WsHeader* hdr, int k, double* sh,
-                                                   double* G) {
-    for (int c = 0; c < d; ++c) {
+// Step k's gradient (one block per step): the sums of the d rows (k, c) of block
+// partials in a fixed order, then g_k = nu u_k + B^T (sum / M); a non-finite entry
+// raises the flag.  Row c is summed by 4 / min(d', 4) waves (d' = 1, 2, 4: d rounded
+// up; one wave takes several rows beyond 4) and wave sums, with one barrier
+// for all rows: a block-wide tree per row cost its eight barriers d times.
+__global__ void __launch_bounds__(kThreads)
+k_finalize_grad(const double* __restrict__ part, int nblk, int D, int d, int64_t M, double nu,
+                const double* __restrict__ u, BMat B, double* __restrict__ g, WsHeader* hdr,
+                Gate gate) {
+    if (gate_closed(gate))
+        return;
+    constexpr int NW = kThreads / 64;
+    __shared__ double G[8][NW];
+    const int k = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), lane = threadIdx.x % 64;
+    const int per = d == 1 ? NW : d == 2 ? NW / 2 : 1;  // waves of a row
+    const int seg = wave % per;
+    for (int c = wave / per; c < d; c += NW / per) {
         const double* row = part + (size_t)(k * D + c) * nblk;
         double s = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kThreads)
+        for (int b = seg * 64 + lane; b < nblk; b += per * 64)
             s += row[b];
-        s = block_sum(s, sh);
-        if (threadIdx.x == 0)
-            G[c] = s / (double)M;
+        s = wave_sum(s);
+        if (lane == 0)
+            G[c][seg] = s;
     }
     __syncthreads();
     const int i = threadIdx.x;
     if (i < d) {
         double v = 0.0;
-        for (int j = 0; j < d; ++j)
-            v += B.b[j * d + i] * G[j];
+        for (int j = 0; j < d; ++j) {
+            double s = 0.0;
+            for (int q = 0; q < per; ++q)
+                s += G[j][q];
+            v += B.b[j * d + i] * (s / (double)M);
+        }
         const double gi = nu * u[(size_t)k * d + i] + v;
         g[(size_t)k * d + i] = gi;
         if (!isfinite(gi))
@@ -1087,76 +1100,71 @@ __device__ __forceinline__ void finalize_grad_step(const double* __restrict__ pa
     }
 }
 
-// One block per step k.
-__global__ void __launch_bounds__(kThreads)
-k_finalize_grad(const double* __restrict__ part, int nblk, int D, int d, int64_t M, double nu,
-                const double* __restrict__ u, BMat B, double* __restrict__ g, WsHeader* hdr,
-                Gate gate) {
-    if (gate_closed(gate))
-        return;
-    __shared__ double sh[kThreads];
-    __shared__ double G[8];
-    finalize_grad_step(part, nblk, D, d, M, nu, u, B, g, hdr, blockIdx.x, sh, G);
-}
-
 // J = (1/M) sum C + nu dt/2 sum |u|^2, and if g is given also dt sum |g|^2
-// (one block); flags non-finite results, then runs the line-search tail.
-__device__ __forceinline__ void finalize_cost_block(const double* __restrict__ cpart, int nblk,
-                                                    int64_t M, double nu, double dt,
-                                                    const double* __restrict__ u, const double* g,
-                                                    int nd, double* J_out, WsHeader* hdr, int slot,
-                                                    const LsTail& tail, double* sh) {
-    double s = 0.0;
-    for (int b = threadIdx.x; b < nblk; b += kThreads)
-        s += cpart[b];
-    const double csum = block_sum(s, sh);
-    double uu = 0.0;
-    for (int q = threadIdx.x; q < nd; q += kThreads)
-        uu += u[q] * u[q];
-    uu = block_sum(uu, sh);
-    double gg = 0.0;
-    int bad = 0;
-    if (g != nullptr) {
-        for (int q = threadIdx.x; q < nd; q += kThreads) {
-            gg += g[q] * g[q];
-            bad |= !isfinite(g[q]);
-        }
-        gg = block_sum(gg, sh);
-        bad = (int)block_sum((double)bad, sh);
-    }
-    if (threadIdx.x == 0) {
-        const double J = csum / (double)M + 0.5 * nu * dt * uu;
-        if (slot == 0) {
-            hdr->J = J;
-            if (g != nullptr)
-                hdr->gnorm2 = dt * gg;
-        } else {
-            hdr->J_trial = J;
-        }
-        if (J_out != nullptr)
-            *J_out = J;
-        // a trial's cost (slot 1) may overflow: the Armijo test rejects it
-        if (slot == 0 && (!isfinite(J) || bad))
-            hdr->nonfinite = 1;
-        if (tail.mode == kLsTailAfterGrad)
-            ls_after_grad_step(hdr, tail.n);
-    }
-    if (tail.mode == kLsTailArmijo) {
-        __shared__ double Jt;
-        if (threadIdx.x == 0)
-            Jt = hdr->J_trial;
-        armijo_step<kThreads>(hdr, tail, &Jt, sh);
-    }
-}
+// (one block); flags non-finite results, then runs the line-search tail.  Bound by
+// the latency of its loads and sums: 1024 threads, all sums by wave and then
+// together through LDS.
+constexpr int kCostThreads = 1024;
 
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kCostThreads)
 k_finalize_cost(const double* __restrict__ cpart, int nblk, int64_t M, double nu, double dt,
                 const double* __restrict__ u, const double* __restrict__ g, int nd,
                 double* __restrict__ J_out, WsHeader* hdr, int slot, Gate gate, LsTail tail) {
     if (gate_closed(gate))
         return;
-    __shared__ double sh[kThreads];
-    finalize_cost_block(cpart, nblk, M, nu, dt, u, g, nd, J_out, hdr, slot, tail, sh);
+    constexpr int W = kCostThreads / 64;
+    __shared__ double sh[kCostThreads];  // sh[3 w + q]: sum q of wave w
+    __shared__ double sum[3];
+    double s = 0.0, uu = 0.0, gg = 0.0;
+    for (int b = threadIdx.x; b < nblk; b += kCostThreads)
+        s += cpart[b];
+    for (int q = threadIdx.x; q < nd; q += kCostThreads)
+        uu += u[q] * u[q];
+    if (g != nullptr) {
+        for (int q = threadIdx.x; q < nd; q += kCostThreads)
+            gg += g[q] * g[q];
+        gg = wave_sum(gg);
+    }
+    s = wave_sum(s);
+    uu = wave_sum(uu);
+    if (threadIdx.x % 64 == 0) {
+        double* w = sh + threadIdx.x / 64 * 3;
+        w[0] = s;
+        w[1] = uu;
+        w[2] = gg;
+    }
+    __syncthreads();
+    if (threadIdx.x < 3) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < W; ++w)
+            t += sh[3 * w + threadIdx.x];
+        sum[threadIdx.x] = t;
+    }
+    __syncthreads();
+    const double J = sum[0] / (double)M + 0.5 * nu * dt * sum[1];
+    if (threadIdx.x == 0) {
+        // slot 0; a trial's cost (slot 1) may overflow: the Armijo test rejects
+        // it (a non-finite entry of g has raised the flag already)
+        if (slot == 0) {
+            hdr->J = J;
+            if (g != nullptr)
+                hdr->gnorm2 = dt * sum[2];
+            if (!isfinite(J))
+                hdr->nonfinite = 1;
+        } else {
+            hdr->J_trial = J;
+        }
+        if (J_out != nullptr)
+            *J_out = J;
+        if (tail.mode == kLsTailAfterGrad)
+            ls_after_grad_step(hdr, tail.n);
+    }
+    if (tail.mode == kLsTailArmijo) {
+        if (threadIdx.x == 0)
+            sum[0] = J;
+        armijo_step<kCostThreads>(hdr, tail, sum, sh);
+    }
 }
 
 __global__ void k_ls_start(WsHeader* hdr) {
@@ -1511,7 +1519,7 @@ hipError_t launch_finalize_cost(const HostProblem& p, const HostRun& r, const do
     t.mode = kLsTailNone;
     if (tail != nullptr)
         t = *tail;
-    hipLaunchKernelGGL(k_finalize_cost, dim3(1), dim3(kThreads), 0, st, cpart, r.nblk, r.M, p.nu,
+    hipLaunchKernelGGL(k_finalize_cost, dim3(1), dim3(kCostThreads), 0, st, cpart, r.nblk, r.M, p.nu,
                        p.dt, u, g, p.N * p.d, J_out, hdr, slot, gate, t);
     return hipGetLastError();
 }
