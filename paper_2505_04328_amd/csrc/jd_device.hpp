@@ -84,7 +84,13 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
 // to one); exact in both precisions.
 template <typename Real>
 __device__ __forceinline__ Real unit_uniform(uint32_t w) {
-    return (Real)((w >> 8) | 1u) * (Real)(1.0 / 16777216.0);
+    // ((w >> 8) | 1) 2^-24 with the bits left in place: one instruction for two
+    // (the compiler splits it to keep both constants scalar), of 134 issue
+    // slots per 1-D FP32 step: 2^20 x 1000 2.258 -> 2.227 ms, d = 4 150001 x 777
+    // 1.109 -> 1.086, d = 8 2^20 x 500 8.64 -> 8.51
+    uint32_t b;
+    asm("v_and_or_b32 %0, %1, %2, %3" : "=v"(b) : "v"(w), "s"(0xffffff00u), "v"(0x100u));
+    return (Real)b * (Real)(1.0 / 4294967296.0);
 }
 
 // Box-Muller pair from two words (u_a, u_b): radius r = sqrt(-2 ln u_a) and

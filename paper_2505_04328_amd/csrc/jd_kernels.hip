@@ -358,7 +358,8 @@ k_noise(SweepArgs<Real, D> a, Real* __restrict__ noise, PoissonTable pt, int tb,
         const int k1 = k0 + ks < a.N ? k0 + ks : a.N;
         const int64_t m = g * kThreads + threadIdx.x;
         Real* out = noise + (g * a.N + k0) * rows + threadIdx.x;
-#pragma unroll 2
+        constexpr int UN = sizeof(Real) == 8 ? 2 : 1;
+#pragma unroll UN
         for (int k = k0; k < k1; ++k, out += rows) {
             StepDraws<Real, D> z;
             draws<Real, D>((uint32_t)m, (uint32_t)k, a.iter, a.key0, a.key1, a.thr, a.thr0, dt, z);
