@@ -297,6 +297,16 @@ __device__ __forceinline__ void row_control_grad(const FbArgs<Real>& a, const Re
     uv *= (Real)-2 * a.eps;
 }
 
+// The control alone, as fb_control.
+template <typename Real, int NVP, int W>
+__device__ __forceinline__ Real row_control(const FbArgs<Real>& a, const Real (&m)[NVP], int j,
+                                            Real x, Real v) {
+    const Real bx = bump_q(fma(-(Real)j, a.eps * a.dxc, a.eps * (x - a.xc0)));
+    const Real pv = bump_q(fma(-(Real)j, a.eps * a.dvc, a.eps * (v - a.vc0)));
+    const Real t = row_dot<Real, NVP>(m, pv, (Real)0);
+    return row_sum<Real, W>(bx, t);
+}
+
 // Receives the shape-function values a step computes, and the control u
 // (the wave transposes of the gradient reduction); NoSink drops them.
 struct NoSink {

@@ -12,7 +12,8 @@
 //                      on the matrix cores of the path precision
 //  k_fb_forward_grad   the surrogate gradient's forward: forward sweep plus
 //                      the control term of the gradient, nothing stored
-//  k_fb_forward_adapted, k_fb_adjoint_adapted, k_fb_adjoint_adapted_rows
+//  k_fb_forward_adapted, k_fb_forward_adapted_sub, k_fb_adjoint_adapted,
+//  k_fb_adjoint_adapted_rows
 //                      the same on the jump-adapted grid (sub-steps between
 //                      each particle's jump times, a stack of post-jump states)
 //  k_fb_finalize_grad  fixed-order FP64 sum of the per-block gradient partials
@@ -427,13 +428,179 @@ k_fb_adjoint(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict
     }
 }
 
-// Forward sweep on the jump-adapted grid, one particle per lane: every
-// interval's sub-steps and jumps (lanes without jumps take one step), the
-// running cost of each sub-step; the trajectory holds the uniform points.
-// FP64 held to three waves per SIMD (two without the bound: ja2 38.5 against
-// 36.4 ms).
+// Forward sweep on the jump-adapted grid where few particles jump in an interval
+// (fb_fwd_row_jumps): sub-step 0 of every particle, one per lane, then the sub-steps
+// after a jump, whose controls are evaluated in rows of 16 lanes (four particles at
+// a time, lane j the shape functions j) for the few particles that have them.
+// Bound by instruction issue: k_fb_forward_adapted lets lanes run an interval
+// ahead instead, for which every lane picks each coefficient from two intervals'
+// rows (100 selects per step) and most iterations run the jump's draws.
+// FP32 8.04 -> 6.93 ms on 2^20 particles x 500 steps (16 x 16 grid 21.3 -> 10.8), FP64
+// 6.63 -> 5.69 on 2^18 x 500, 0.49 -> 0.38 on 50000 x 50.
 template <typename Real, int NVP, bool STORE>
 __global__ void __launch_bounds__(kThreads, (sizeof(Real) == 8 ? 3 : 1))
+k_fb_forward_adapted_sub(FbArgs<Real> a, const Real* __restrict__ mu,
+                         const Real* __restrict__ zd, void* traj, double* __restrict__ cpart) {
+    if (gate_closed(a.gate))
+        return;
+    __shared__ PoissonTable thr;
+    fb_stage_thresholds(a, &thr);
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
+    __shared__ double sh[kThreads];
+    // the interval's control rows for the row evaluation, loaded an interval
+    // ahead and put in the wave's LDS when an interval needs them
+    constexpr int NM = (kFbMaxGrid * NVP + 63) / 64;
+    __shared__ Real mrow[kFbWaves][kFbMaxGrid * NVP];
+    Real* const mw = mrow[threadIdx.x >> 6];
+    const int ln = threadIdx.x & 63, lj = ln & 15;
+    const int nm = a.nx * NVP;
+    Real pm[NM];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int q = 0; q < NM; ++q) {
+            const int e = q * 64 + ln;
+            pm[q] = mu[(size_t)k * nm + (e < nm ? e : 0)];
+        }
+    };
+    fetch(0);
+    const FbSlot sl = fb_slot<1>(a, 0);
+    Real x, v, cx = 0, cv = 0;
+    fb_initial(a, sl.p, x, v);
+    Real* row = STORE ? fb_row<Real>(traj, a.N, blockIdx.x) : nullptr;
+    if (STORE) {
+        __builtin_nontemporal_store(x, row);
+        __builtin_nontemporal_store(v, row + kThreads);
+    }
+    fb_dump(a, a.dX, 0, sl.p, x, v);
+    FbJumps<Real> jumps;
+    int nj = 0;
+    if (STORE)
+        jumps = fb_jumps<Real>(traj, a.N, a.nblk);
+    double acc = 0.0;
+    for (int k = 0; k < a.N; ++k) {
+        const Real* mk = mu + (size_t)k * nm;
+        const Real* zk = zd + 2 * k;
+        Real zx, zv, a1;
+        const int n = fb_interval(a, sl.p, k, zx, zv, a1);
+        if (STORE)
+            __builtin_nontemporal_store((uint8_t)n, jumps.per + (size_t)k * kThreads);
+        const uint64_t any = __builtin_amdgcn_ballot_w64(n > 0);
+        // the jump that ends sub-step r < n, at offset a1
+        auto jump = [&](int r) {
+            Real S;
+            fb_jump_draws(a, sl.p, k, r, S, zx, zv);
+            v = fma(S, a.sbeta, a.gamma * v);
+            cv = a.gamma * cv;
+            if (STORE) {
+                if (nj < kFbJumpCap) {
+                    jumps.st[(size_t)(kFbJumpComp * nj) * kThreads] = x;
+                    jumps.st[(size_t)(kFbJumpComp * nj + 1) * kThreads] = v;
+                    jumps.st[(size_t)(kFbJumpComp * nj + 2) * kThreads] = a1;
+                }
+            }
+            ++nj;
+        };
+        {
+            const Real u = fb_control<Real, NVP>(a, mk, x, v);
+            Real d = a.dt, ha = a.hadt, sq1 = a.sqb1, sq2 = a.sqb2;
+            if (any != 0 && n > 0) {
+                d = a1 * a.dt;
+                ha = (Real)0.5 * a.alpha * d;
+                const Real s = sqrt(d);
+                sq1 = a.b1 * s;
+                sq2 = a.b2 * s;
+            }
+            acc += (double)(ha * u * u);
+            fb_euler(a, d, sq1, sq2, u, zx, zv, x, v, cx, cv);
+            Real tg[2] = {zk[2], zk[3]};
+            if (any != 0 && n > 0) {
+                jump(0);
+                fb_target(zk, a1, tg);
+            }
+            acc += (double)(d * track(a, x, v, tg));
+        }
+        if (any != 0) {
+            wave_lds_sync();
+#pragma unroll
+            for (int q = 0; q < NM; ++q)
+                if (q * 64 + ln < nm)
+                    mw[q * 64 + ln] = pm[q];
+            wave_lds_sync();
+            Real m[NVP];  // lane j: control row j (zeros past the grid)
+#pragma unroll
+            for (int l = 0; l < NVP; ++l)
+                m[l] = lj < a.nx ? mw[lj * NVP + l] : (Real)0;
+            for (int r = 1;; ++r) {
+                const uint64_t live = __builtin_amdgcn_ballot_w64(r <= n);
+                if (live == 0)
+                    break;
+                // four live lanes at a time, in their order: the i-th in row i
+                Real u = 0;
+                int pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(live >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo((uint32_t)live, 0u));
+                uint64_t left = live;
+                do {
+                    int src = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int s = left != 0 ? __builtin_ctzll(left) : 0;
+                        left &= left - 1;
+                        src = ln >= 16 * i ? s : src;
+                    }
+                    const Real xq = __shfl(x, src), vq = __shfl(v, src);
+                    Real uq;
+                    if (a.nx <= 10)
+                        uq = row_control<Real, NVP, 10>(a, m, lj, xq, vq);
+                    else
+                        uq = row_control<Real, NVP, 16>(a, m, lj, xq, vq);
+                    const Real ul = __shfl(uq, 16 * (pos & 3));
+                    u = pos >= 0 && pos < 4 ? ul : u;
+                    pos -= 4;
+                } while (left != 0);
+                if (r <= n) {
+                    const Real a0 = a1;
+                    a1 = r < n ? fb_next_offset(a, sl.p, k, r, n, a0) : (Real)1;
+                    const Real d = (a1 - a0) * a.dt;
+                    const Real s = sqrt(d);
+                    acc += (double)((Real)0.5 * a.alpha * d * u * u);
+                    fb_euler(a, d, a.b1 * s, a.b2 * s, u, zx, zv, x, v, cx, cv);
+                    if (r < n)
+                        jump(r);
+                    Real tg[2];
+                    fb_target(zk, a1, tg);
+                    acc += (double)(d * track(a, x, v, tg));
+                }
+            }
+        }
+        if (k + 1 < a.N)
+            fetch(k + 1);
+        if (STORE) {
+            Real* rw = row + (size_t)(k + 1) * 2 * kThreads;
+            __builtin_nontemporal_store(x, rw);
+            __builtin_nontemporal_store(v, rw + kThreads);
+        }
+        fb_dump(a, a.dX, k + 1, sl.p, x, v);
+    }
+    if (STORE)
+        *jumps.count = nj;
+    const double C = sl.act ? acc : 0.0;
+    if (a.dcost != nullptr) {
+        const int64_t p = (int64_t)sl.p - a.dm0;
+        if (sl.act && p >= 0 && p < a.dcount)
+            a.dcost[p] = C;
+    }
+    const double s = block_sum(C, sh);
+    if (threadIdx.x == 0)
+        cpart[blockIdx.x] = s;
+}
+
+// Forward sweep on the jump-adapted grid, one particle per lane: every
+// interval's sub-steps and jumps (lanes without jumps take one step), the
+// running cost of each sub-step; the trajectory holds the uniform points.  FP32
+// paths only (fb_forward_sub).
+template <typename Real, int NVP, bool STORE>
+__global__ void __launch_bounds__(kThreads)
 k_fb_forward_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
                      void* traj, double* __restrict__ cpart) {
     if (gate_closed(a.gate))
@@ -749,7 +916,7 @@ k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
     }
 }
 
-// The same sweep where few particles jump in an interval (fb_row_jumps) and every
+// The adjoint sweep where few particles jump in an interval (fb_row_jumps) and every
 // jump is on the stack (blocks with a particle past it return and are left to
 // k_fb_adjoint_adapted).  A sub-step after a jump belongs to few of the wave's
 // particles (ja2: 1.1 per interval); evaluated in every lane it doubled the
@@ -1231,6 +1398,18 @@ hipError_t fb_launch_table(const FbHost& p, const HostRun& r, const double* mu, 
     return hipGetLastError();
 }
 
+// Which forward the jump-adapted grid takes.  FP64 paths evaluate the sub-steps after
+// a jump in rows at every count and rate (rows / lanes one interval ahead, 2^18
+// particles: 5.69 / 6.63 ms at 0.018 jumps per interval, 0.97 / 1.05 at 2).  FP32 paths
+// from 131072 particles on, where other waves hide the rows' latency, and up to
+// half a jump per interval: 2^20 particles 6.93 / 8.04 ms at 0.018, 1.20 / 1.28 at 0.18,
+// 0.73 / 0.76 at 0.45, 1.84 / 1.81 at 0.93; 2^18 0.586 / 0.609 at 0.089, 131072 1.336 /
+// 1.337 at 0.018, 65536 1.10 / 1.05.
+template <typename Real>
+static bool fb_forward_sub(const FbHost& p, const HostRun& r) {
+    return sizeof(Real) == 8 || (p.rate * p.dt <= 0.5 && r.M >= 131072);
+}
+
 template <typename Real>
 static hipError_t fb_forward_t(const FbHost& p, const HostRun& r, const void* tab, void* traj,
                                double* cpart, const WsHeader* hdr, hipStream_t st, Gate gate) {
@@ -1242,6 +1421,7 @@ static hipError_t fb_forward_t(const FbHost& p, const HostRun& r, const void* ta
     a.gate = gate;
     const Real* tb = (const Real*)tab;
     const unsigned nb = (unsigned)fb_forward_blocks(p, r);
+    const bool sub = fb_forward_sub<Real>(p, r);
 #define FB_FWD_K(NVP, S, GG, RG, TPB)                                                             \
     hipLaunchKernelGGL((k_fb_forward<Real, NVP, S, GG, RG, TPB>), dim3(nb), dim3(TPB), 0, st, a,  \
                        tb + t.mu, tb + t.zd, tb + t.ks, traj, cpart)
@@ -1253,8 +1433,14 @@ static hipError_t fb_forward_t(const FbHost& p, const HostRun& r, const void* ta
                       fb_ring_fwd_threads<Real>());                                               \
     } while (0)
 #define FB_FWD_A(NVP, S)                                                                          \
-    hipLaunchKernelGGL((k_fb_forward_adapted<Real, NVP, S>), dim3(nb), dim3(kThreads), 0, st, a,  \
-                       tb + t.mu, tb + t.zd, traj, cpart)
+    do {                                                                                          \
+        if (sub)                                                                                  \
+            hipLaunchKernelGGL((k_fb_forward_adapted_sub<Real, NVP, S>), dim3(nb),                \
+                               dim3(kThreads), 0, st, a, tb + t.mu, tb + t.zd, traj, cpart);      \
+        else if constexpr (sizeof(Real) == 4)                                                     \
+            hipLaunchKernelGGL((k_fb_forward_adapted<Real, NVP, S>), dim3(nb), dim3(kThreads), 0, \
+                               st, a, tb + t.mu, tb + t.zd, traj, cpart);                         \
+    } while (0)
 #define FB_FWD(NVP)                                                                               \
     do {                                                                                          \
         if (p.grid == 1) {                                                                        \

@@ -32,18 +32,6 @@
 namespace jd {
 
 // ---------------------------------------------------------------------------
-// The feedback control of the row's particle at (x, v), as fb_control: lane j
-// holds row j of the step's coefficients in m (zeros past the grid; a zero
-// term leaves a sum as it is).
-template <typename Real, int W>
-__device__ __forceinline__ Real row_control(const FbArgs<Real>& a, const Real (&m)[W], int j,
-                                            Real x, Real v) {
-    const Real bx = bump_q(fma(-(Real)j, a.eps * a.dxc, a.eps * (x - a.xc0)));
-    const Real pv = bump_q(fma(-(Real)j, a.eps * a.dvc, a.eps * (v - a.vc0)));
-    const Real t = row_dot<Real, W>(m, pv, (Real)0);
-    return row_sum<Real, W>(bx, t);
-}
-
 // Draws of one step: the Box-Muller cosine and sine branches, and the step's jumps
 // v <- gn v + sv zj (without jumps gn = 1 and sv zj = -0, which leaves v as it is).
 template <typename Real>
@@ -258,7 +246,7 @@ k_fb_forward_rows(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __res
             if (RING && j == 0)
                 xs[k & 1][row] = x;
             Real cpl = 0;
-            const Real u = row_control<Real, W>(a, m, j, x, v);
+            const Real u = row_control<Real, W, W>(a, m, j, x, v);
             if (RING) {
                 lds_barrier();
                 const Real* xb = xs[k & 1];
@@ -443,7 +431,7 @@ k_fb_forward_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
 #pragma unroll
             for (int c = 0; c < W; ++c)
                 m[c] = mus[k - kb][j < W ? j : 0][c];
-            const Real u = row_control<Real, W>(a, m, j, x, v);
+            const Real u = row_control<Real, W, W>(a, m, j, x, v);
             acc += (double)((whole ? a.hadt : (Real)0.5 * a.alpha * len) * u * u);
             fb_euler(a, len, whole ? a.sqb1 : a.b1 * sqrt(len), whole ? a.sqb2 : a.b2 * sqrt(len),
                      u, zx, zv, x, v, cx, cv);

@@ -84,12 +84,12 @@ int fb_ring_groups(int np) { return np <= kBlock ? 1 : 8; }
 // 242 at 47100.  Rings of 500 and 2000: FP32 267 / 334 at 96000, 345 / 334 at 128000;
 // FP64 850 / 1084 at 128000, 1054 / 1084 at 160000.  Jump-adapted grid (0.18 jumps per
 // interval): FP32 68 / 205 at 2000, 159 / 199 at 28672, 198 / 199 at 32768 (at 0.93
-// per interval 235 / 232); FP64 93 / 488 at 2000, 380 / 488 at 32768, 478 / 488 at 40960.
+// per interval 235 / 232); FP64 93 / 378 at 2000, 340 / 378 at 28672, 380 / 378 at 32768.
 static int64_t fb_small_forward_max(const FbHost& p, const HostRun& r) {
     if (p.np > 1 && p.G > 1)
         return r.prec == JD_FP64 ? 147456 : 114688;
     if (p.grid == 1)
-        return r.prec == JD_FP64 ? 32768 : 28672;
+        return 28672;
     if (p.np > 1)
         return r.prec == JD_FP64 ? 32768 : 40960;
     return 49152;
