@@ -178,7 +178,7 @@ def serving_main(args):
 def kernel_source_hash() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("jd_device.hpp", "jd_kernels.hip", "jd_launch.hpp"):
+    for f in ("jd_device.hpp", "jd_draw_table.hpp", "jd_kernels.hip", "jd_launch.hpp"):
         with open(os.path.join(ROOT, "paper_2505_04328_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -204,7 +204,8 @@ def profiled_traffic(kernel: str):
 def fb_source_hash() -> str:
     import hashlib
     h = hashlib.sha256()
-    for f in ("fb_kernels.hip", "fb_launch.hpp", "jd_device.hpp"):
+    for f in ("fb_device.hpp", "fb_kernels.hip", "fb_launch.hpp", "fb_small.hip", "jd_device.hpp",
+              "jd_draw_table.hpp"):
         with open(os.path.join(ROOT, "paper_2505_04328_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]

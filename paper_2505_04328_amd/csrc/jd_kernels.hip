@@ -182,8 +182,7 @@ struct BMat {
 // at idx < 32 the header's thresholds and flags.  g != nullptr: a line-search
 // trial.  The table is built for ut = u - zeta g, which the lanes of
 // components i < d also write out (each lane evaluates the trial entries of
-// its row with k_trial's expression, so the table and ut are bitwise those of
-// k_trial followed by the plain table).
+// its row with the same expression).
 template <typename Real, int D>
 __device__ __forceinline__ void table_entry(int idx, const double* __restrict__ u,
                                             const double* __restrict__ xd, Real* __restrict__ tab,
