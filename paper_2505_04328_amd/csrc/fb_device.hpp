@@ -647,6 +647,24 @@ __device__ __forceinline__ uint32_t fb_live_products(uint64_t live) {
     return (uint32_t)(live | live >> 16 | live >> 32 | live >> 48) & 0xFFFFu;
 }
 
+// The products that hold more than one of them.
+__device__ __forceinline__ uint32_t fb_shared_products(uint64_t live) {
+    const uint32_t a = (uint32_t)live & 0xFFFFu, b = (uint32_t)(live >> 16) & 0xFFFFu;
+    const uint32_t c = (uint32_t)(live >> 32) & 0xFFFFu, d = (uint32_t)(live >> 48);
+    return (a & b) | ((a | b) & (c | d)) | (c & d);
+}
+
+// A value that the 16 lanes of row i hold alike, in every lane.
+__device__ __forceinline__ float row_value(float x, int i) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), 16 * i));
+}
+__device__ __forceinline__ double row_value(double x, int i) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, 16 * i);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 16 * i);
+    return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+
 template <typename Real, int VR>
 struct FbWave {
     typedef typename FbMma<Real>::acc_t acc_t;

@@ -921,13 +921,16 @@ k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
 // k_fb_adjoint_adapted).  A sub-step after a jump belongs to few of the wave's
 // particles (ja2: 1.1 per interval); evaluated in every lane it doubled the
 // kernel's work (1022 VALU instructions per interval against 512).  Here the
-// sub-steps r >= 1 are evaluated by rows of 16 lanes: the matrix-core product q
-// takes particles 16 kk + q, so row kk evaluates that particle, lane j its shape
-// functions j, and the lanes' values are the product's operands as they stand
-// (no LDS transposes).  The operations, and the products in their order, are
+// sub-steps r >= 1 are evaluated by rows of 16 lanes, a particle per row, lane j its
+// shape functions j, and the lanes' values are the operands of the matrix-core
+// products as they stand (no LDS transposes).  Product q takes particles 16 kk + q: a
+// round evaluates up to four products of one particle each (a product's sum
+// does not depend on the row of its only particle) or one product that rows
+// share.  The operations, and the products in their order, are
 // k_fb_adjoint_adapted's (whose products with no live particle add zeros).
-// ja2 adjoint: FP32 15.4 -> 11.5 ms (0.73 of it the fixed grid's 8.4 ms), at four
-// waves per SIMD (five spill: 13.0 ms); 2^18 FP64 particles 12.05 -> 7.35 ms.
+// ja2 adjoint: FP32 15.4 -> 11.3 ms (fixed grid: 8.3), at four waves per SIMD (five
+// spill: 13.0 ms), 11.5 with a product per round; 2^20 x 100 4.1 -> 3.4 (3.9); 2^18 FP64
+// particles x 500 12.05 -> 7.35 ms.
 template <typename Real, int NVP>
 __global__ void __launch_bounds__(kThreads, (sizeof(Real) == 4 ? 4 : 2))
 k_fb_adjoint_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
@@ -1036,11 +1039,29 @@ k_fb_adjoint_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
             const Real share = sa - a0;  // the sub-step's share d / dt of the step
             const uint64_t live = __builtin_amdgcn_ballot_w64(mine && sl.act);
             uint32_t qm = fb_live_products(live);
+            const uint32_t many = fb_shared_products(live);
             Real u = 0, ux = 0, uv = 0;
             while (qm != 0) {
-                const int q = __builtin_ctz(qm);
-                qm &= qm - 1;
-                const int src = (ln & 48) | q;
+                // the round's particles: of one product that several rows share, or
+                // of up to four products with one particle each, the i-th in row i
+                int src, lane[4], cnt = 0;
+                if (many >> __builtin_ctz(qm) & 1) {
+                    src = (ln & 48) | __builtin_ctz(qm);
+                    qm &= qm - 1;
+                } else {
+                    src = 0;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        lane[i] = -1;
+                        if (cnt == i && qm != 0 && !(many >> __builtin_ctz(qm) & 1)) {
+                            lane[i] =
+                                __builtin_ctzll(live & 0x0001000100010001ull << __builtin_ctz(qm));
+                            qm &= qm - 1;
+                            cnt = i + 1;
+                            src = ln >= 16 * i ? lane[i] : src;
+                        }
+                    }
+                }
                 const Real xq = __shfl(x, src), vq = __shfl(v, src);
                 const Real lq = __shfl(lvm, src), sq = __shfl(share, src);
                 Real bx, pv, uq, uxq, uvq;
@@ -1049,12 +1070,30 @@ k_fb_adjoint_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
                 else
                     row_control_grad<Real, NVP, 16>(a, m, lj, xq, vq, bx, pv, uq, uxq, uvq);
                 const Real wk = sq * fma(a.alpha, uq, lq);
-                wave.acc = FbMma<Real>::mfma(bx, pv * ((live >> src) & 1 ? wk : (Real)0),
-                                             wave.acc);
-                if (lj == q) {
-                    u = uq;
-                    ux = uxq;
-                    uv = uvq;
+                if (cnt == 0) {
+                    wave.acc = FbMma<Real>::mfma(bx, pv * ((live >> src) & 1 ? wk : (Real)0),
+                                                 wave.acc);
+                    if (ln == src) {
+                        u = uq;
+                        ux = uxq;
+                        uv = uvq;
+                    }
+                } else {
+                    const Real pw = pv * wk;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (i < cnt) {
+                            wave.acc = FbMma<Real>::mfma(bx, ln >> 4 == i ? pw : (Real)0, wave.acc);
+                            // row i's values to its particle's lane
+                            const Real ui = row_value(uq, i), uxi = row_value(uxq, i),
+                                       uvi = row_value(uvq, i);
+                            if (ln == lane[i]) {
+                                u = ui;
+                                ux = uxi;
+                                uv = uvi;
+                            }
+                        }
+                    }
                 }
             }
             if (mine) {
@@ -1465,12 +1504,13 @@ hipError_t fb_launch_forward(const FbHost& p, const HostRun& r, const void* tab,
 
 // Jumps per particle and interval up to which the jump-adapted adjoint evaluates
 // the sub-steps after a jump in rows: with more of them a pass over the whole
-// wave costs less than one row evaluation per product.  Rows / whole wave on 2^20
-// FP32 particles: 11.5 / 15.4 ms at 0.018 (500 steps), 5.87 / 7.10 at 0.045, 3.87 / 4.08
-// at 0.089, 3.26 / 3.19 at 0.127, 2.77 / 2.53 at 0.18; on 2^18 FP64 particles: 7.35 /
-// 12.05 at 0.018, 2.19 / 3.08 at 0.089, 1.13 / 1.30 at 0.30, 0.94 / 1.00 at 0.45.
+// wave costs less than a row evaluation per four particles.  Rows / whole wave on 2^20
+// FP32 particles: 11.3 / 15.5 ms at 0.018 (500 steps), 5.32 / 7.13 at 0.045, 3.37 / 4.11 at
+// 0.089, 2.36 / 2.54 at 0.18, 2.12 / 2.24 at 0.22, 1.91 / 1.85 at 0.30 (70000 particles 0.415 /
+// 0.442 at 0.18, 0.369 / 0.369 at 0.22); on 2^18 FP64 particles: 7.35 / 12.1 at 0.018, 2.01 /
+// 3.06 at 0.089, 1.06 / 1.30 at 0.30, 0.89 / 0.99 at 0.45, 1.55 / 1.11 at 0.91.
 template <typename Real>
-constexpr double fb_row_jumps() { return sizeof(Real) == 4 ? 0.1 : 0.45; }
+constexpr double fb_row_jumps() { return sizeof(Real) == 4 ? 0.2 : 0.45; }
 
 template <typename Real>
 static hipError_t fb_adjoint_t(const FbHost& p, const HostRun& r, const void* tab, const void* traj,

@@ -63,7 +63,8 @@ def test_small_adapted_counts_match_oracle(dev, case, precision):
 
 # (the larger count: the forward with the sub-steps after a jump in rows)
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
-@pytest.mark.parametrize("M,N,T", [(28672, 18, 1.8), (28673, 2, 0.1), (49152, 1, 0.05)])
+@pytest.mark.parametrize("M,N,T", [(28672, 18, 1.8), (28673, 2, 0.1), (49152, 1, 0.05),
+                                   (20000, 30, 1.0)])
 def test_small_and_large_adapted_counts_agree_bitwise(dev, M, N, T, precision):
     from paper_2505_04328_amd import binding as B
     p = _problem(N, T=T)
