@@ -731,19 +731,12 @@ __device__ __forceinline__ bool fb_past_stack(const void* traj, int N, int64_t n
 // the interval's start only past the stack's capacity), each adding d_r/dt
 // phi(z_r) (alpha u_r + lam^v_-) to the matrix-core sums; lam^v_- carries the
 // jump factor gamma.
-// Held to four waves per SIMD in FP32 (three without the bound: ja2 19.9
-// against 18.3 ms) and two in FP64 (one without: 80.0 against 54.8 ms).
 template <typename Real, int NVP>
-__global__ void __launch_bounds__(kThreads, (sizeof(Real) == 4 ? 4 : 2))
-k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
-                     const void* traj, double* __restrict__ apart, bool past_stack) {
-    if (gate_closed(a.gate))
-        return;
-    if (past_stack && !fb_past_stack<Real>(traj, a.N, a.nblk))
-        return;
-    __shared__ DrawLds<Real> dl;
-    a.dtab = dl.stage();
-    __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
+__device__ __forceinline__ void fb_adapted_sweep(const FbArgs<Real>& a,
+                                                 const Real* __restrict__ mu,
+                                                 const Real* __restrict__ zd, const void* traj,
+                                                 double* __restrict__ apart,
+                                                 FbShared<Real, fb_vrows<NVP>()>& sh) {
     auto wave = fb_wave(sh);
     constexpr int H = fb_adj_hold<Real, NVP>(4);
     FbHist<Real, H> hist;
@@ -916,9 +909,27 @@ k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __
     }
 }
 
-// The adjoint sweep where few particles jump in an interval (fb_row_jumps) and every
-// jump is on the stack (blocks with a particle past it return and are left to
-// k_fb_adjoint_adapted).  A sub-step after a jump belongs to few of the wave's
+// past_stack: only the blocks with a particle past its jump stack.  Held to four
+// waves per SIMD in FP32 (three without the bound: ja2 19.9 against 18.3 ms) and two
+// in FP64 (one without: 80.0 against 54.8 ms).
+template <typename Real, int NVP>
+__global__ void __launch_bounds__(kThreads, (sizeof(Real) == 4 ? 4 : 2))
+k_fb_adjoint_adapted(FbArgs<Real> a, const Real* __restrict__ mu, const Real* __restrict__ zd,
+                     const void* traj, double* __restrict__ apart, bool past_stack) {
+    if (gate_closed(a.gate))
+        return;
+    if (past_stack && !fb_past_stack<Real>(traj, a.N, a.nblk))
+        return;
+    __shared__ DrawLds<Real> dl;
+    a.dtab = dl.stage();
+    __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
+    fb_adapted_sweep<Real, NVP>(a, mu, zd, traj, apart, sh);
+}
+
+// The adjoint sweep where few particles jump in an interval (fb_row_jumps).  Blocks
+// with a particle past its jump stack run the general sweep beside the others: in
+// a launch of its own one such block (about 1 in 10 calls at ja2's size has one)
+// took 3.4 ms, here 0.65; without one the second sweep costs 1%.  A sub-step after a jump belongs to few of the wave's
 // particles (ja2: 1.1 per interval); evaluated in every lane it doubled the
 // kernel's work (1022 VALU instructions per interval against 512).  Here the
 // sub-steps r >= 1 are evaluated by rows of 16 lanes, a particle per row, lane j its
@@ -938,9 +949,19 @@ k_fb_adjoint_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
                           double* __restrict__ apart) {
     if (gate_closed(a.gate))
         return;
-    if (fb_past_stack<Real>(traj, a.N, a.nblk))
-        return;
     __shared__ FbShared<Real, fb_vrows<NVP>()> sh;
+    // the waves' control rows, or the general sweep's draw table (FP64)
+    constexpr size_t RB = kFbWaves * kFbMaxGrid * NVP * sizeof(Real);
+    constexpr size_t DB = sizeof(Real) == 8 ? sizeof(DrawTable) : 0;
+    __shared__ alignas(16) char rows[RB > DB ? RB : DB];
+    if (__builtin_expect(fb_past_stack<Real>(traj, a.N, a.nblk), 0)) {
+        if constexpr (sizeof(Real) == 8) {
+            stage_draw_table((DrawTable*)rows);
+            a.dtab = (const DrawTable*)rows;
+        }
+        fb_adapted_sweep<Real, NVP>(a, mu, zd, traj, apart, sh);
+        return;
+    }
     auto wave = fb_wave(sh);
     constexpr int H = fb_adj_hold<Real, NVP>(4);
     FbHist<Real, H> hist;
@@ -950,8 +971,7 @@ k_fb_adjoint_adapted_rows(FbArgs<Real> a, const Real* __restrict__ mu,
     // the interval's control rows for the row evaluation, loaded an interval
     // ahead and put in the wave's LDS when an interval needs them
     constexpr int NM = (kFbMaxGrid * NVP + 63) / 64;
-    __shared__ Real mrow[kFbWaves][kFbMaxGrid * NVP];
-    Real* const mw = mrow[threadIdx.x >> 6];
+    Real* const mw = (Real*)rows + (threadIdx.x >> 6) * (kFbMaxGrid * NVP);
     const int ln = threadIdx.x & 63, lj = ln & 15;
     const int nm = a.nx * NVP;
     Real pm[NM];
@@ -1541,8 +1561,9 @@ static hipError_t fb_adjoint_t(const FbHost& p, const HostRun& r, const void* ta
             if (rows)                                                                             \
                 hipLaunchKernelGGL((k_fb_adjoint_adapted_rows<Real, NVP>), dim3(nb),              \
                                    dim3(kThreads), 0, st, a, tb + t.mu, tb + t.zd, traj, apart);  \
-            hipLaunchKernelGGL((k_fb_adjoint_adapted<Real, NVP>), dim3(nb), dim3(kThreads), 0,    \
-                               st, a, tb + t.mu, tb + t.zd, traj, apart, rows || small);          \
+            else                                                                                  \
+                hipLaunchKernelGGL((k_fb_adjoint_adapted<Real, NVP>), dim3(nb), dim3(kThreads),   \
+                                   0, st, a, tb + t.mu, tb + t.zd, traj, apart, small);           \
         } else if (p.np > 1) {                                                                    \
             if (G == 8) {                                                                         \
                 constexpr int RT = fb_ring_adj_threads<Real, NVP>();                              \
